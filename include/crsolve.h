@@ -257,7 +257,9 @@ int crsolve_set_graphs(crsolve_plan *plan, int enable);
  * times, on the given data, the two kernel variants of each level role --
  * one-wave/MFMA kernels and work-group kernels -- for the elimination, the
  * reduced-system formation and the back substitution, and keeps the faster
- * one (synchronizes; overwrites x and the workspace).  Blocks of 33..64 have
+ * one (synchronizes; overwrites x and the workspace).  Blocks of 9..32 have
+ * one kernel for the elimination and one for the back substitution (both
+ * variants name it; the token is 0).  Blocks of 33..64 have
  * one elimination and one back-substitution kernel (tiled) and two variants
  * of the reduced-system formation (16 x 16 tiles, or one wave per block), so
  * only that role is tuned for them; blocks above 64 have one kernel per role

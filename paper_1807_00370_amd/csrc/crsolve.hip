@@ -184,7 +184,9 @@ struct crsolve_plan {
     }
 
     // kernel variant per (role: elim, reduce, back; class; precision):
-    // 0 = one-wave / MFMA kernels, 1 = work-group kernels (autotuner)
+    // 0 = one-wave / MFMA kernels, 1 = work-group kernels (autotuner).  Blocks
+    // of 9..32 are eliminated and substituted back by the MFMA kernels either
+    // way: the work-group forms were never the faster ones there.
     int var[3][kNumCls][2] = {};
     // launch shapes of the levels with few blocks (autotuner): waves per
     // level for the split elimination, block count below which the reduced
@@ -278,16 +280,17 @@ struct Disp {
                      const void* iny, void* W, unsigned long long* flags, int mat, int rhs,
                      hipStream_t st, int variant, int nsplit)
     {
-        if ((MT == 16 || MT == 32) && variant == 0) {
-            hipLaunchKernelGGL((crs::k_elim_mf<T, (MT == 16 || MT == 32) ? MT : 16, EI>),
+        if constexpr (MT == 16 || MT == 32) {
+            hipLaunchKernelGGL((crs::k_elim_mf<T, MT, EI>),
                                dim3((unsigned)(L.total * nsplit)), dim3(64), 0, st,
                                segs + L.seg0, L.nseg, L.total, nsplit, (const EI*)inA,
                                (const EI*)inB, (const EI*)iny, (cx<T>*)W, flags, mat, rhs);
-        } else if (MT <= 32 && variant == 0) {
-            hipLaunchKernelGGL((crs::k_elim_w<T, MT <= 32 ? MT : 32, EI>), dim3((unsigned)L.total), dim3(64), 0, st,
+        } else if constexpr (MT > 32) { // blocks above 32 run the tiled kernels
+        } else if (variant == 0) {
+            hipLaunchKernelGGL((crs::k_elim_w<T, MT, EI>), dim3((unsigned)L.total), dim3(64), 0, st,
                                segs + L.seg0, L.nseg, L.total, (const EI*)inA,
                                (const EI*)inB, (const EI*)iny, (cx<T>*)W, flags, mat, rhs);
-        } else if constexpr (MT <= 32) { // blocks above 32 run the tiled kernels
+        } else {
             constexpr int PW = sizeof(T) == 8 ? 32 : 64;
             hipLaunchKernelGGL((crs::k_elim<T, MT, kNT, PW, EI>), dim3(grid_of(L.total)), dim3(kNT), 0,
                                st, segs + L.seg0, L.nseg, L.total, (const EI*)inA,
@@ -318,8 +321,8 @@ struct Disp {
                      const unsigned long long* flags, hipStream_t st, int variant, void* U,
                      int upd)
     {
-        if ((MT == 16 || MT == 32) && variant == 0) {
-            hipLaunchKernelGGL((crs::k_back_mf<T, (MT == 16 || MT == 32) ? MT : 16>), dim3((unsigned)L.total), dim3(64), 0, st,
+        if constexpr (MT == 16 || MT == 32) {
+            hipLaunchKernelGGL((crs::k_back_mf<T, MT>), dim3((unsigned)L.total), dim3(64), 0, st,
                                segs + L.seg0, L.nseg, L.total, (const cx<T>*)W, (cx<T>*)X, flags,
                                (cx<double>*)U, upd);
         } else if constexpr (MT <= 32) { // blocks above 32 run the tiled kernels
@@ -422,9 +425,6 @@ void run_elim(const Ctx& c, const Launch& L, const void* A, const void* B, const
         const BigDims b = big_dims(c.p, L);
         if (mat) {
             Timed tm(c.p, KID_POTRF, c.st, L.cls, L.f64);
-            // levels with at most one block per CU spread the panel tiles over
-            // eight waves instead of four
-            const unsigned nthr = L.total <= kPotrfWideBlocks ? 512 : 256;
             if (L.total <= kPotrfWideBlocks)
                 // few blocks (every tiled class): one block's chain of panels
                 // sets the time, so the diagonal steps run ahead of the
@@ -432,12 +432,8 @@ void run_elim(const Ctx& c, const Launch& L, const void* A, const void* B, const
                 hipLaunchKernelGGL((crs::k_potrf_rl<T, EI, RE>), dim3((unsigned)L.total), dim3(512), 0,
                                    c.st, c.dsegs + L.seg0, L.nseg, L.total, (const EI*)inA,
                                    (cx<T>*)c.ws, c.flags);
-            else if (L.cls == kBig)
-                hipLaunchKernelGGL((crs::k_potrf_big<T, false, EI, RE>), dim3((unsigned)L.total), dim3(nthr), 0,
-                                   c.st, c.dsegs + L.seg0, L.nseg, L.total, (const EI*)inA,
-                                   (cx<T>*)c.ws, c.flags);
             else
-                hipLaunchKernelGGL((crs::k_potrf_big<T, true, EI, RE>), dim3((unsigned)L.total), dim3(nthr), 0,
+                hipLaunchKernelGGL((crs::k_potrf_big<T, EI, RE>), dim3((unsigned)L.total), dim3(256), 0,
                                    c.st, c.dsegs + L.seg0, L.nseg, L.total, (const EI*)inA,
                                    (cx<T>*)c.ws, c.flags);
         }
@@ -477,7 +473,7 @@ void run_elim(const Ctx& c, const Launch& L, const void* A, const void* B, const
     Timed tm(c.p, KID_ELIM, c.st, L.cls, L.f64);
     const int v = c.p->var[0][L.cls][L.f64];
     int nsplit = 1;
-    if (mf_class(L.cls) && v == 0) {
+    if (mf_class(L.cls)) {
         const BigDims b = big_dims(c.p, L);
         const int nst = (mat ? 2 * b.S : 0) + (rhs ? b.K16 : 0);
         nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(nst, c.p->tail_waves / L.total));
@@ -1935,9 +1931,11 @@ int crsolve_autotune(crsolve_plan* p, const void* A, const void* B, const void* 
         for (int c = 0; c < kNumCls; ++c)
             for (int f = 0; f < 2; ++f) {
                 // tiled classes have one elimination and one back-substitution
-                // kernel, and above 64 one reduced-system form as well
+                // kernel, and above 64 one reduced-system form as well; the
+                // classes of 9..32 also have one of each (their token is 0)
                 const bool tuned = seen[r][c][f] && !(tiled(c) && r != 1) && c != kBig;
-                const int v = (tuned && t[1][r][c][f] < t[0][r][c][f]) ? 1 : 0;
+                const bool both = tuned && !(mf_class(c) && r != 1);
+                const int v = (both && t[1][r][c][f] < t[0][r][c][f]) ? 1 : 0;
                 p->var[r][c][f] = v;
                 if (tuned)
                     out += "r" + std::to_string(r) + "c" + std::to_string(c) + "f" +

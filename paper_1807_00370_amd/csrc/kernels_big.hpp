@@ -279,97 +279,41 @@ __device__ __forceinline__ void zero_acc(typename MF<T>::v4 (&cr)[RM][RN],
 }
 
 // The diagonal step of panel I of the tiled Cholesky, run by one wave: the
-// tile S_II (lower triangle in sT, leading dimension 17) is factored by the
-// left-looking lane-per-row Cholesky, lane r & 15 keeping row r in registers
-// and the later columns reading the finished rows by broadcast (scalar
-// registers for RB, else LDS over sT); then lane r forms column r of
-// D_I = L_II^{-1} by forward substitution.  L_II goes to L (diagonal
+// tile S_II (lower triangle in sT, leading dimension 17) is factored and
+// inverted in the registers (tile_chol).  L_II goes to L (diagonal
 // {L_cc, 1 / L_cc}), D_I to Dg and to sD (leading dimension 17).  Returns
 // true on a pivot that is not > 0.
-template <class T, bool RB>
+template <class T, bool RE>
 __device__ __forceinline__ bool potrf_diag_tile(cx<T>* sT, cx<T>* sD, cx<T>* __restrict__ Lg,
                                                 cx<T>* __restrict__ Dg, int m, int I)
 {
-    const int lane = threadIdx.x & 63, c0 = 16 * I;
+    const int lane = threadIdx.x & 63, kr = lane >> 4, c0 = 16 * I;
     const int r = lane & 15, gi = c0 + r;
-    const bool real = gi < m;
-    cx<T> a[16];
+    cx<double> t[4], l[4], e[4];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-        if (real)
-            a[u] = u <= r ? sT[r * 17 + u] : czero<T>();
-        else
-            a[u] = u == r ? cx<T>{T(1), T(0)} : czero<T>();
-        if (u == r)
-            a[u].i = T(0);
+    for (int v = 0; v < 4; ++v) {
+        const int u = kr + 4 * v;
+        t[v] = cvt<double>(sT[r * 17 + u]);
+        if (gi >= m)
+            t[v] = cx<double>{u == r ? 1.0 : 0.0, 0.0};
     }
-    bool fail = false;
+    const bool fail = tile_chol<T, RE>(t, l, e, m - c0);
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-        cx<T> s0 = a[c], s1 = czero<T>();
-#pragma unroll
-        for (int u = 0; u + 1 < c; u += 2) {
-            if constexpr (RB) {
-                msub_cb(s0, a[u], lane_bcast(a[u], c));
-                msub_cb(s1, a[u + 1], lane_bcast(a[u + 1], c));
-            } else {
-                msub_cb(s0, a[u], sT[c * 17 + u]);
-                msub_cb(s1, a[u + 1], sT[c * 17 + u + 1]);
-            }
-        }
-        if (c & 1)
-            msub_cb(s0, a[c - 1], RB ? lane_bcast(a[c - 1], c) : sT[c * 17 + c - 1]);
-        const cx<T> sv{s0.r + s1.r, s0.i + s1.i};
-        const T dg = RB ? lane_bcast(sv.r, c) : __shfl(sv.r, c);
-        const T inv = rsqrt_nr(dg);
-        const T sq = dg * inv;
-        fail |= (c0 + c < m) && !(dg > T(0));
-        if (r == c)
-            a[c] = cx<T>{sq, inv}; // inverse pivot kept in the imaginary slot
-        else if (r > c)
-            a[c] = cx<T>{sv.r * inv, sv.i * inv};
-        if constexpr (!RB) {
-            if (lane < 16)
-                sT[r * 17 + c] = a[c];
-            wave_lds_sync();
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    if (lane < 16 && real) {
-#pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (u <= r)
-                Lg[(int64_t)gi * m + c0 + u] = a[u];
-    }
-    cx<T> z[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        cx<T> v = q == r ? cx<T>{T(1), T(0)} : czero<T>();
-#pragma unroll
-        for (int u = 0; u < q; ++u)
-            msub(v, RB ? lane_bcast(a[u], q) : sT[q * 17 + u], z[u]);
-        const T iq = RB ? lane_bcast(a[q].i, q) : sT[q * 17 + q].i;
-        z[q] = cx<T>{v.r * iq, v.i * iq};
-    }
-    if (lane < 16) {
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            Dg[I * 256 + q * 16 + r] = z[q];
-            sD[q * 17 + r] = z[q];
-        }
+    for (int v = 0; v < 4; ++v) {
+        const int u = kr + 4 * v;
+        const cx<T> d = cvt<T>(e[v]);
+        sD[u * 17 + r] = d;
+        Dg[I * 256 + u * 16 + r] = d;
+        if (gi < m && u <= r)
+            Lg[(int64_t)gi * m + c0 + u] = cvt<T>(l[v]);
     }
     return fail;
 }
 
 // ------------------------------------------------------------- k_potrf_big
 
-// RB: the diagonal tile's Cholesky and inverse read the rows of L through
-// the scalar registers (lane c broadcasts row c) and the kernel is held to
-// three waves per SIMD; otherwise the rows go through LDS and the compiler
-// keeps two waves per SIMD.  The first is faster at m <= 64 (the diagonal
-// tiles are a larger share of the work), the second at m = 256.
-template <class T, bool RB, class EI = cx<T>, bool RE = false>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(RB ? 3 : 2, 8))) void k_potrf_big(const Seg* __restrict__ segs, int nseg,
+template <class T, class EI = cx<T>, bool RE = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_potrf_big(const Seg* __restrict__ segs, int nseg,
                                                    int64_t total, const EI* __restrict__ inA,
                                                    cx<T>* __restrict__ W,
                                                    unsigned long long* __restrict__ flags)
@@ -418,13 +362,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(RB ? 3 : 2,
             }
         }
         __syncthreads();
-        // diagonal tile (wave 0): lane r & 15 keeps row r in registers;
-        // left-looking Cholesky whose later columns read the finished rows
-        // of L by broadcast (scalar registers, or LDS over S_I, already in
-        // registers); then lane r forms column r of D = L_II^{-1} by forward
-        // substitution
+        // diagonal tile: L_II and D_I (wave 0)
         if (wv == 0) {
-            const bool fail = potrf_diag_tile<T, RB>(sT, sD, Lg, Dg, m, I);
+            const bool fail = potrf_diag_tile<T, RE>(sT, sD, Lg, Dg, m, I);
             if (lane == 0 && fail)
                 sFail = 1;
         }
@@ -527,7 +467,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
                 sT[i * 17 + cc] = e;
         }
         wave_lds_sync();
-        fail |= potrf_diag_tile<T, false>(sT, sD, Lg, Dg, m, 0);
+        fail |= potrf_diag_tile<T, RE>(sT, sD, Lg, Dg, m, 0);
     }
     __syncthreads();
     for (int I = 0; I < S; ++I) {
@@ -583,7 +523,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
                         sT[i * 17 + cc] = cx<T>{o.r - acc.re(0, 0, v), o.i - acc.im(0, 0, v)};
                 }
                 wave_lds_sync();
-                fail |= potrf_diag_tile<T, false>(sT, sD, Lg, Dg, m, J);
+                fail |= potrf_diag_tile<T, RE>(sT, sD, Lg, Dg, m, J);
             } else {
                 // the other trailing tiles S_RC -= L_RI L_CI^H, I < C <= R, row
                 // by row (tile 0 is the look-ahead's), TB at a time: their

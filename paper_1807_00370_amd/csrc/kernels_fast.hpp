@@ -13,9 +13,8 @@
 //               form), operands loaded from HBM straight into the MFMA lane
 //               layout; diagonal blocks are written as their lower triangle
 //               only (the Hermitian reading every consumer uses).
-//   k_elim_mf   (8 < m <= 32) the Cholesky with each row's dot products
-//               split over the wave's lane groups, then the substitutions
-//               on MFMA with the inverses of the 16 x 16 diagonal tiles.
+//   k_elim_mf   (8 < m <= 32) the Cholesky by 16 x 16 tiles (tile_chol), then
+//               the substitutions on MFMA with the inverse diagonal tiles.
 //   k_back_mf   w = g - Q x_{p-d} - P x_{p+d} on MFMA, then L^H x = w tile by
 //               tile on MFMA with the inverse diagonal tiles.
 #pragma once
@@ -117,39 +116,19 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// x[l] + x[l ^ 32] in every lane l, through the gfx950 swap of the upper
-// half of one register with the lower half of another (one VALU instruction
-// per dword, no LDS round trip).  Swapping x with itself leaves one result
-// holding the lower half's values in both halves and the other the upper
-// half's, so their sum is the same, bit for bit, in every lane.
-__device__ __forceinline__ float sum_xor32(float x)
+// Value of x in lane N of each 16-lane row, in every lane of that row: one
+// data-parallel move per dword pair (the row broadcast of the gfx9 matrix
+// GPUs), no scalar registers and no LDS round trip.
+template <int N>
+__device__ __forceinline__ double row_bcast(double x)
 {
-    const unsigned v = __float_as_uint(x);
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    return __builtin_amdgcn_update_dpp(x, x, 0x150 + N, 0xf, 0xf, true);
 }
-__device__ __forceinline__ double sum_xor32(double x)
+template <int N>
+__device__ __forceinline__ float row_bcast(float x)
 {
-    const unsigned long long v = (unsigned long long)__double_as_longlong(x);
-    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(v >> 32), (unsigned)(v >> 32), false, false);
-    return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
-           __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
-}
-// x[l] + x[l ^ 16], the same way with the swap of odd and even 16-lane rows.
-__device__ __forceinline__ float sum_xor16(float x)
-{
-    const unsigned v = __float_as_uint(x);
-    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ double sum_xor16(double x)
-{
-    const unsigned long long v = (unsigned long long)__double_as_longlong(x);
-    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(v >> 32), (unsigned)(v >> 32), false, false);
-    return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
-           __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+    const int v = __float_as_int(x);
+    return __int_as_float(__builtin_amdgcn_update_dpp(v, v, 0x150 + N, 0xf, 0xf, true));
 }
 
 // MFMA 16x16x4 lane layout (wave64, checked on gfx950): lane l supplies
@@ -337,6 +316,260 @@ __device__ __forceinline__ void tile_nn3(Acc3<T, 1, 1>& acc, const cx<T>* __rest
     }
 }
 
+// --------------------------------------------------- 16 x 16 tiles in registers
+
+// Cholesky factor L and inverse D = L^{-1} of one 16 x 16 tile by one wave, on
+// registers and MFMA.  Lane (kr, cc) = (lane / 16, lane % 16) keeps the four
+// entries u = kr + 4 v of row cc of the tile: this is the accumulator layout
+// of the FP64 16x16x4 instruction for the transposed tile, and register v
+// over the four lane groups is the panel of the columns 4 v .. 4 v + 3.  Per
+// panel of four columns:
+//   - every lane gathers its row's four panel entries (lane swaps) and
+//     factors the panel on its own row, pivots and finished columns coming by
+//     row broadcasts;
+//   - beside it lane group k eliminates column k of the panel's identity,
+//     which leaves M = [D_pp; -L_below D_pp], one entry per lane;
+//   - one 4-term product on MFMA updates the whole trailing tile,
+//     S -= L_p L_p^H (the lane's own entry of L_p is both operands), and one
+//     more all of D, D_{p..} = M D_p (the lane's own accumulator is the right
+//     operand).
+// A panel's chain is four pivots long; the 16 x 16 updates leave it.  The
+// chain of dependent FP64 operations bounds it.  Measured, FP64 complex, one
+// wave: 5560 cycles for L and D; a column at a time on the vector unit, every
+// lane on its whole row, 8700 with twice the instructions.  In an elimination
+// of 64 blocks of m = 32 the two tiles and the products between them take
+// 6.8 us where the forms they replaced (the dot products split over lane
+// groups with LDS broadcasts, then D by substitution from LDS) took 10.8 us;
+// the diagonal step of the tiled Cholesky went from 7.8 to about 2.5 us
+// (16 blocks of m = 64: k_potrf_rl 45 -> 26 us).
+//
+// The tile is factored in double for every type; for float the columns are
+// rounded to float as they are finished, so that D is the inverse of the L
+// that is stored.
+template <class T>
+__device__ __forceinline__ double round_to(double x)
+{
+    return sizeof(T) == 8 ? x : (double)(float)x;
+}
+
+// o[g] = x of the lane with the same cc in lane group g.
+__device__ __forceinline__ void gather_groups(double x, double (&o)[4])
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    unsigned w[2] = {(unsigned)b, (unsigned)(b >> 32)}, q[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        // odd 16-lane rows of the first operand swap with even rows of the
+        // second, then upper and lower halves
+        const auto t = __builtin_amdgcn_permlane16_swap(w[i], w[i], false, false);
+        const auto e = __builtin_amdgcn_permlane32_swap(t[0], t[0], false, false);
+        const auto d = __builtin_amdgcn_permlane32_swap(t[1], t[1], false, false);
+        q[i][0] = e[0];
+        q[i][1] = d[0];
+        q[i][2] = e[1];
+        q[i][3] = d[1];
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        o[g] = __longlong_as_double((long long)(((unsigned long long)q[1][g] << 32) | q[0][g]));
+}
+
+// Column C = 4 P + J of the panel's identity: row C is scaled by the inverse
+// pivot, the rows below subtract their L_rC times it.
+template <int C, bool RE>
+__device__ __forceinline__ void tile_inv_col(cx<double>& q, const cx<double> l, double inv, int r)
+{
+    const cx<double> z{row_bcast<C>(q.r) * inv, RE ? 0.0 : row_bcast<C>(q.i) * inv};
+    const cx<double> lm{r > C ? l.r : 0.0, RE ? 0.0 : (r > C ? l.i : 0.0)};
+    cx<double> t{fma(-lm.r, z.r, q.r), 0.0};
+    if constexpr (!RE) {
+        t.r = fma(lm.i, z.i, t.r);
+        t.i = fma(-lm.r, z.i, q.i);
+        t.i = fma(-lm.i, z.r, t.i);
+    }
+    q.r = r == C ? z.r : t.r;
+    if constexpr (!RE)
+        q.i = r == C ? z.i : t.i;
+}
+
+template <class T, bool RE, int P, int J>
+__device__ __forceinline__ void tile_chol_col(cx<double> (&c)[4], cx<double>& q, int r,
+                                              int mr, unsigned long long& fail)
+{
+    constexpr int C = 4 * P + J;
+    const double d = row_bcast<C>(c[J].r);
+    const double inv = round_to<T>(rsqrt_nr(d));
+    fail |= C < mr ? __ballot(!(d > 0.0)) : 0ull;
+    asm volatile("" : "+s"(fail)); // compared now, not with all 16 pivots kept
+    const cx<double> l{round_to<T>(c[J].r * inv), RE ? 0.0 : round_to<T>(c[J].i * inv)};
+    auto sub = [&](cx<double>& x, double ur, double ui) { // x -= l conj(u)
+        x.r = fma(-l.r, ur, x.r);
+        if constexpr (!RE) {
+            x.r = fma(-l.i, ui, x.r);
+            x.i = fma(-l.i, ur, x.i);
+            x.i = fma(l.r, ui, x.i);
+        }
+    };
+    if constexpr (J < 1)
+        sub(c[1], row_bcast<4 * P + 1>(l.r), RE ? 0.0 : row_bcast<4 * P + 1>(l.i));
+    if constexpr (J < 2)
+        sub(c[2], row_bcast<4 * P + 2>(l.r), RE ? 0.0 : row_bcast<4 * P + 2>(l.i));
+    if constexpr (J < 3)
+        sub(c[3], row_bcast<4 * P + 3>(l.r), RE ? 0.0 : row_bcast<4 * P + 3>(l.i));
+    tile_inv_col<C, RE>(q, l, inv, r);
+    c[J] = l;
+}
+
+// D over panel P: rows of the panel are replaced, the rows below updated.
+template <bool RE, int P>
+__device__ __forceinline__ void tile_inv_panel(d4v& er, d4v& ei, const cx<double> q)
+{
+    const double br = er[P], bi = RE ? 0.0 : ei[P];
+    er[P] = 0.0;
+    er = MF<double>::mma(q.r, br, er);
+    if constexpr (!RE) {
+        ei[P] = 0.0;
+        ei = MF<double>::mma(q.r, bi, ei);
+        er = MF<double>::mma(-q.i, bi, er);
+        ei = MF<double>::mma(q.i, br, ei);
+    }
+}
+
+template <class T, bool RE, int P>
+__device__ __forceinline__ void tile_chol_panel(d4v& sr, d4v& si, d4v& er, d4v& ei, cx<double> (&L)[4],
+                                                int r, int g, int mr,
+                                                unsigned long long& fail)
+{
+    cx<double> c[4], q{r == 4 * P + g ? 1.0 : 0.0, 0.0};
+    double xr[4], xi[4] = {0, 0, 0, 0};
+    gather_groups(sr[P], xr);
+    if constexpr (!RE)
+        gather_groups(si[P], xi);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        c[j] = cx<double>{xr[j], xi[j]};
+    tile_chol_col<T, RE, P, 0>(c, q, r, mr, fail);
+    tile_chol_col<T, RE, P, 1>(c, q, r, mr, fail);
+    tile_chol_col<T, RE, P, 2>(c, q, r, mr, fail);
+    tile_chol_col<T, RE, P, 3>(c, q, r, mr, fail);
+    const bool b0 = g & 1, b1 = g & 2;
+    cx<double> l;
+    l.r = b1 ? (b0 ? c[3].r : c[2].r) : (b0 ? c[1].r : c[0].r);
+    l.i = RE ? 0.0 : (b1 ? (b0 ? c[3].i : c[2].i) : (b0 ? c[1].i : c[0].i));
+    L[P] = l;
+    if constexpr (P < 3) {
+        sr = MF<double>::mma(-l.r, l.r, sr);
+        if constexpr (!RE) {
+            si = MF<double>::mma(-l.r, l.i, si);
+            sr = MF<double>::mma(-l.i, l.i, sr);
+            si = MF<double>::mma(l.i, l.r, si);
+        }
+    }
+    tile_inv_panel<RE, P>(er, ei, q);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+__device__ __forceinline__ void tile_identity(d4v& er, d4v& ei, int r, int g)
+{
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        er[v] = g + 4 * v == r ? 1.0 : 0.0;
+    ei = d4v{0, 0, 0, 0};
+}
+
+// s: the lane's entries (cc, kr + 4 v) of the tile (those right of the
+// diagonal may hold anything) -> L: the same entries of the factor, the
+// diagonal as {L_rr, 1 / L_rr}; e: entries (kr + 4 v, cc) of D.  Returns true
+// if one of the first mr pivots is not > 0 (the same in every lane).
+template <class T, bool RE = false>
+__device__ __forceinline__ bool tile_chol(const cx<double> (&s)[4], cx<double> (&L)[4],
+                                          cx<double> (&e)[4], int mr)
+{
+    const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
+    d4v sr, si, er, ei;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        sr[v] = s[v].r;
+        si[v] = s[v].i;
+    }
+    tile_identity(er, ei, r, g);
+    unsigned long long fail = 0;
+    tile_chol_panel<T, RE, 0>(sr, si, er, ei, L, r, g, mr, fail);
+    tile_chol_panel<T, RE, 1>(sr, si, er, ei, L, r, g, mr, fail);
+    tile_chol_panel<T, RE, 2>(sr, si, er, ei, L, r, g, mr, fail);
+    tile_chol_panel<T, RE, 3>(sr, si, er, ei, L, r, g, mr, fail);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        e[v] = cx<double>{er[v], ei[v]};
+        if (g + 4 * v == r) // the inverse pivot is D's diagonal
+            L[v].i = er[v];
+    }
+    return fail != 0;
+}
+
+// Storage of a factor of 8 < m <= 32 (in LDS and in the workspace): the packed
+// lower triangle, row r at r (r + 1) / 2, with L_10 in its place and the
+// inverse diagonal tiles D_I in place of L_II.  D_I is as large as L_II, and
+// no later pass needs L_II itself.
+
+// The lane's entries (cc, kr + 4 v) of diagonal tile I of such a triangle of
+// A (entries right of the diagonal: the diagonal's), identity rows past m.
+template <class T>
+__device__ __forceinline__ void tile_load(const cx<T>* sL, int I, int m, cx<double> (&s)[4])
+{
+    const int lane = threadIdx.x & 63, kr = lane >> 4, r = lane & 15, gi = 16 * I + r;
+    const cx<T>* row = sL + gi * (gi + 1) / 2 + 16 * I;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        s[v] = cvt<double>(row[min(kr + 4 * v, r)]);
+        if (gi >= m)
+            s[v] = cx<double>{kr + 4 * v == r ? 1.0 : 0.0, 0.0};
+    }
+}
+// D_I (entries (kr + 4 v, cc), as tile_chol leaves them) into the triangle.
+template <class T>
+__device__ __forceinline__ void tile_store(cx<T>* sL, int I, int m, const cx<double> (&e)[4])
+{
+    const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int q = kr + 4 * v, gi = 16 * I + q;
+        if (gi < m && cc <= q)
+            sL[gi * (gi + 1) / 2 + 16 * I + cc] = cvt<T>(e[v]);
+    }
+}
+// Operands of the MFMA products: D_I[cc][MF::row(kr, v)] (adj: the conjugate
+// of D_I[MF::row(kr, v)][cc]).  Rows past m are identity rows.
+template <class T, bool adj>
+__device__ __forceinline__ void tile_operand(const cx<T>* sL, int I, int m, cx<T> (&aD)[4])
+{
+    const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int q = MF<T>::row(kr, v), i = adj ? q : cc, j = adj ? cc : q, gi = 16 * I + i;
+        const cx<T> x = sL[gi * (gi + 1) / 2 + 16 * I + min(i, j)];
+        const bool ok = gi < m && j <= i;
+        aD[v] = ok ? cx<T>{x.r, adj ? -x.i : x.i} : cx<T>{gi >= m && i == j ? T(1) : T(0), T(0)};
+    }
+}
+// The packed triangle between memory and LDS, a lane's elements e = lane +
+// 64 q: all loads issued before the first is used; lanes past the end move the
+// last element (the same value), so no branch holds one back.
+template <class T, int MT>
+__device__ __forceinline__ void packed_load(cx<T>* sL, const cx<T>* __restrict__ L, int m)
+{
+    constexpr int NE = (MT * (MT + 1) / 2 + 63) / 64;
+    const int lane = threadIdx.x & 63, np = m * (m + 1) / 2;
+    cx<T> x[NE];
+#pragma unroll
+    for (int q = 0; q < NE; ++q)
+        x[q] = L[min(lane + 64 * q, np - 1)];
+#pragma unroll
+    for (int q = 0; q < NE; ++q)
+        sL[min(lane + 64 * q, np - 1)] = x[q];
+    wave_lds_sync();
+}
+
 // ----------------------------------------------------------------- k_elim_w
 
 template <class T, int MT, class EI = cx<T>>
@@ -512,58 +745,30 @@ __global__ __launch_bounds__(64, (col_waves<T, MT>())) void k_elim_w(const Seg* 
     }
 }
 
-// Replaces the packed lower triangle L (m <= 16 S, diagonal {L_cc, 1/L_cc})
-// held in LDS by the inverses D_I = L_II^{-1} of its 16 x 16 diagonal tiles,
-// sL[I * 256 + q * 16 + j] = D_I[q][j]: lane j < 16 S forms column j & 15 of
-// D_{j / 16} by forward substitution (padded rows are identity rows).  Every
-// lane of the work-group must call it.
-template <class T, int S>
-__device__ __forceinline__ void inverse_tiles_lds(cx<T>* sL, int m)
-{
-    const int lane = threadIdx.x & 63;
-    const int I0 = (lane >> 4) < S ? (lane >> 4) : 0, jj = lane & 15;
-    cx<T> z[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int gq = 16 * I0 + q;
-        cx<T> v = q == jj ? cx<T>{T(1), T(0)} : czero<T>();
-        if (gq < m) {
-            const int base = gq * (gq + 1) / 2 + 16 * I0;
-#pragma unroll
-            for (int u = 0; u < q; ++u)
-                msub(v, sL[base + u], z[u]);
-            const T iq = sL[base + q].i;
-            v = cx<T>{v.r * iq, v.i * iq};
-        }
-        z[q] = v;
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    __syncthreads(); // every read of L in LDS is done
-    if (lane < 16 * S) {
-#pragma unroll
-        for (int q = 0; q < 16; ++q)
-            sL[I0 * 256 + q * 16 + jj] = z[q];
-    }
-    __syncthreads();
-}
-
 // ---------------------------------------------------------------- k_elim_mf
 
-// Elimination for block sizes 8 < m <= 32 with the forward substitutions on
-// MFMA.  After the Cholesky (its dot products split over the lane groups) the
-// inverses D_I = L_II^{-1} of the 16 x 16 diagonal tiles are formed, and each
-// 16-column strip G of [B_p^H | B_{p-d} | y_p] is solved tile by tile,
-// X_0 = D_0 G_0 and
+// Elimination for block sizes 8 < m <= 32 on MFMA.  The Cholesky runs by 16 x
+// 16 tiles: tile_chol of the first gives L_00 and D_0 = L_00^{-1}, then L_10 =
+// A_10 D_0^H, S_11 = A_11 - L_10 L_10^H and tile_chol again.  Each 16-column
+// strip G of [B_p^H | B_{p-d} | y_p] is solved tile by tile, X_0 = D_0 G_0 and
 // X_1 = D_1 (G_1 - L_10 X_0): register v of a lane's accumulator holds row
 // MF::row(kr, v) of its column, which is the right operand of contraction
 // step v when the left operand supplies column MF::row(kr, v), so the
 // products chain through the accumulators.  Right-hand sides are read from
-// memory straight into that layout, each next strip while the current one is
-// solved.
+// memory straight into that layout, the first strip's before the Cholesky,
+// each next strip while the current one is solved.
+//
+// What is stored is L_10 and the D tiles in place of L's diagonal tiles: the
+// later passes (right-hand side alone, back substitution) start with the
+// operands they need and invert nothing.  A level of 64 blocks, m = 32, FP64,
+// k = 16: 20.2 -> 15.9 us with the matrix, 9.8 -> 7.4 us without (2.6 us of
+// that was the inverse); 8192 blocks (bound by HBM): 163 -> 153 us and 49 ->
+// 41 us.  A and the factor move through LDS so that every access to memory is
+// linear: the same loads straight into the tile layout (64-byte pieces) cost
+// 30 % at 8192 blocks.
 //
 // The register budget is held to three waves per SIMD (168 VGPRs for FP64,
-// m = 32, no spills), which hides more of each block's latency than the
-// 196 registers the compiler would take on its own.
+// m = 32, no spills).
 //
 // nsplit waves share a block: wave sp solves strips sp, sp + nsplit, ...
 // Each of them factors the block itself (a few microseconds of latency,
@@ -584,9 +789,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
     using v4 = typename MF<T>::v4;
     constexpr int S = MT / 16;
     constexpr int NP = MT * (MT + 1) / 2;
-    constexpr int NS = NP > S * 256 ? NP : S * 256;
-    __shared__ cx<T> sL[NS]; // packed L, later the D tiles
-    __shared__ int sFail;
+    __shared__ cx<T> sL[NP]; // packed A, then the factor
     const int lane = threadIdx.x, kr = lane >> 4, cc = lane & 15;
     const int64_t w = blockIdx.x / nsplit;
     const int sp = (int)(blockIdx.x - w * nsplit);
@@ -597,7 +800,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
     const int p = s.e0 + (int)t * s.es;
     const int m = s.m, k = s.k, d = s.d;
     const int64_t mm = (int64_t)m * m, mk = (int64_t)m * k;
-    const int np = m * (m + 1) / 2;
     const bool hasPrev = p - d >= 0, hasNext = p + d < s.n;
     if ((flags[s.sys] >> 40) < (unsigned long long)s.level)
         return; // broke down at an earlier level: nothing left to do
@@ -632,126 +834,98 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
     } while (0)
     cx<T> gn[S][4];
 
-    // a lane's elements e = lane + 64 q of the packed lower triangle, all
-    // loads issued before the first is used (one round trip, not NE); lanes
-    // past the end load and store the last element (the same value), so no
-    // branch holds a load back
-    constexpr int NE = (NP + 63) / 64;
+    cx<T> aL[4], aD[S][4]; // left operands: L_10, then the D tiles
+    const int i1 = 16 + cc;
+    cx<T>* row1 = sL + i1 * (i1 + 1) / 2; // row i1 of the triangle
     if (with_mat) {
         const EI* Ap = inA + s.oA + (int64_t)p * mm;
+        const int np = m * (m + 1) / 2;
+        constexpr int NE = (NP + 63) / 64;
         EI av[NE];
 #pragma unroll
         for (int q = 0; q < NE; ++q) {
             const int e = min(lane + 64 * q, np - 1), r = tri_row(e);
             av[q] = Ap[r * m + e - r * (r + 1) / 2];
         }
+        // the first strip's loads return during the factorization
+        if (sp < nst)
+            CRS_LOAD_STRIP(sp, gn);
 #pragma unroll
         for (int q = 0; q < NE; ++q)
             sL[min(lane + 64 * q, np - 1)] = cvt<T>(av[q]);
-        __syncthreads();
-        // left-looking Cholesky with each dot product split over the
-        // G = 64 / MT lane groups: lane g MT + r keeps the entries u = G j + g
-        // of row r (b[j]) and sums the terms u = g (mod G); the groups'
-        // partial sums meet by lane swaps.  Each finished entry L[r][c] goes
-        // to LDS in place of A's (row r is read only by its own lanes), from
-        // where every later column c' reads row c' by broadcast.
-        constexpr int G = 64 / MT, NB = MT / G;
-        const int r = lane % MT, grp = lane / MT;
-        const int rl = r < m ? r : 0;
-        cx<T> b[NB];
+        wave_lds_sync();
+        cx<double> t[4], L[4], e[4];
+        tile_load<T>(sL, 0, m, t);
+        bool fail = tile_chol<T>(t, L, e, m);
+        tile_store<T>(sL, 0, m, e);
+        wave_lds_sync();
+        tile_operand<T, false>(sL, 0, m, aD[0]);
+        if constexpr (S == 2) {
+            // L_10 as a left operand: conj(L_10)^T = D_0 A_10^H comes out of
+            // the products with row MF::row(kr, v) of column cc in register
+            // v, which is conj(L_10[cc][MF::row(kr, v)])
+            v4 zr = {0, 0, 0, 0}, zi = {0, 0, 0, 0};
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const int u = G * j + grp;
-            b[j] = (u <= rl) ? sL[rl * (rl + 1) / 2 + u] : czero<T>();
-        }
-        bool fail = false;
-#pragma unroll
-        for (int c = 0; c < MT; ++c) {
-            if (c < m) {
-                // row c of L (entries u < c final): every read issued before
-                // the first product, so the LDS latency is paid once a column
-                const cx<T>* rc = sL + c * (c + 1) / 2;
-                cx<T> lc[NB];
-#pragma unroll
-                for (int j = 0; j < c / G; ++j)
-                    lc[j] = rc[G * j + grp];
-                if (c % G) // groups g >= c mod G read entry 0 and add zero
-                    lc[c / G] = rc[grp < c % G ? G * (c / G) + grp : 0];
-                __builtin_amdgcn_sched_barrier(0);
-                cx<T> s0 = czero<T>(), s1 = czero<T>();
-#pragma unroll
-                for (int j = 0; j < c / G; ++j) {
-                    if (j & 1)
-                        msub_cb(s1, b[j], lc[j]);
-                    else
-                        msub_cb(s0, b[j], lc[j]);
-                }
-                if (c % G) { // the last terms: groups g < c mod G only
-                    const int j = c / G;
-                    msub_cb(s0, grp < c % G ? b[j] : czero<T>(), lc[j]);
-                }
-                cx<T> sm{s0.r + s1.r, s0.i + s1.i};
-                if (G == 4) {
-                    sm.r = sum_xor16(sm.r);
-                    sm.i = sum_xor16(sm.i);
-                }
-                sm.r = sum_xor32(sm.r);
-                sm.i = sum_xor32(sm.i);
-                // group c mod G holds entry c of every row
-                const int gc = c % G, jc = c / G;
-                const cx<T> v{b[jc].r + sm.r, b[jc].i + sm.i};
-                const T dg = lane_bcast(v.r, gc * MT + c);
-                const T inv = rsqrt_nr(dg);
-                const T sq = dg * inv;
-                fail |= !(dg > T(0));
-                // inverse pivot kept in the imaginary slot of the diagonal
-                const cx<T> l = r == c ? cx<T>{sq, inv} : cx<T>{v.r * inv, v.i * inv};
-                if (grp == gc) {
-                    b[jc] = l;
-                    if (r >= c && r < m)
-                        sL[r * (r + 1) / 2 + c] = l;
-                }
-                wave_lds_sync();
+            for (int v = 0; v < 4; ++v) {
+                const cx<T> x = row1[MF<T>::row(kr, v)], d = aD[0][v];
+                const T br = i1 < m ? x.r : T(0), bi = i1 < m ? -x.i : T(0);
+                zr = MF<T>::mma(d.r, br, zr);
+                zi = MF<T>::mma(d.r, bi, zi);
+                zr = MF<T>::mma(-d.i, bi, zr);
+                zi = MF<T>::mma(d.i, br, zi);
             }
-            __builtin_amdgcn_sched_barrier(0);
+            wave_lds_sync();
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                aL[v] = cx<T>{zr[v], -zi[v]};
+                if (i1 < m)
+                    row1[MF<T>::row(kr, v)] = aL[v];
+            }
+            wave_lds_sync();
+            // S_11 = A_11 - L_10 L_10^H in the layout of tile_chol: the lane's
+            // entries of L_10 are both operands
+            tile_load<T>(sL, 1, m, t);
+            d4v pr, pi;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                pr[v] = t[v].r;
+                pi[v] = t[v].i;
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const cx<double> x = sizeof(T) == 8 ? cvt<double>(aL[v])
+                                                    : (i1 < m ? cvt<double>(row1[kr + 4 * v]) : czero<double>());
+                pr = MF<double>::mma(-x.r, x.r, pr);
+                pi = MF<double>::mma(-x.r, x.i, pi);
+                pr = MF<double>::mma(-x.i, x.i, pr);
+                pi = MF<double>::mma(x.i, x.r, pi);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                t[v] = cx<double>{pr[v], pi[v]};
+            fail |= tile_chol<T>(t, L, e, m - 16);
+            tile_store<T>(sL, 1, m, e);
+            wave_lds_sync();
+            tile_operand<T, false>(sL, 1, m, aD[1]);
         }
-        __syncthreads();
-        if (lane == 0)
-            sFail = fail;
-        if (sp == 0) {
-            if (lane == 0 && sFail)
-                atomicMin(&flags[s.sys], fail_key(s.level, s.ob0 + s.obs * p));
-            for (int e = lane; e < np; e += 64)
-                Lg[e] = sL[e];
-        }
+        if (sp == 0 && lane == 0 && fail)
+            atomicMin(&flags[s.sys], fail_key(s.level, s.ob0 + s.obs * p));
     } else {
-        cx<T> lv[NE];
+        packed_load<T, MT>(sL, Lg, m);
+        if (sp < nst)
+            CRS_LOAD_STRIP(sp, gn);
 #pragma unroll
-        for (int q = 0; q < NE; ++q)
-            lv[q] = Lg[min(lane + 64 * q, np - 1)];
-#pragma unroll
-        for (int q = 0; q < NE; ++q)
-            sL[min(lane + 64 * q, np - 1)] = lv[q];
+        for (int I = 0; I < S; ++I)
+            tile_operand<T, false>(sL, I, m, aD[I]);
     }
-    __syncthreads();
-
-    // left operands: L_10, then the D tiles
-    cx<T> aL[4];
+    if constexpr (S == 2) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int i = 16 + cc, u = MF<T>::row(kr, v);
-        aL[v] = (S == 2 && i < m) ? sL[i * (i + 1) / 2 + u] : czero<T>();
+        for (int v = 0; v < 4; ++v) {
+            const cx<T> x = row1[MF<T>::row(kr, v)];
+            aL[v] = i1 < m ? x : czero<T>();
+        }
     }
-    inverse_tiles_lds<T, S>(sL, m);
-    cx<T> aD[S][4];
-#pragma unroll
-    for (int I = 0; I < S; ++I)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            aD[I][v] = sL[I * 256 + cc * 16 + MF<T>::row(kr, v)];
 
-    if (sp < nst)
-        CRS_LOAD_STRIP(sp, gn);
 #pragma unroll 1
     for (int st = sp; st < nst; st += nsplit) {
         cx<T> g[S][4];
@@ -824,6 +998,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
             }
         }
     }
+    // the factor last: no load waits behind these stores
+    if (with_mat && sp == 0)
+        for (int e = lane; e < m * (m + 1) / 2; e += 64)
+            Lg[e] = sL[e];
 }
 
 #undef CRS_LOAD_STRIP
@@ -1190,8 +1368,7 @@ __global__ __launch_bounds__(64, 2) void k_back_mf(const Seg* __restrict__ segs,
     using v4 = typename MF<T>::v4;
     constexpr int S = MT / 16, KS = MT / 4;
     constexpr int NP = MT * (MT + 1) / 2;
-    constexpr int NS = NP > S * 256 ? NP : S * 256;
-    __shared__ cx<T> sL[NS]; // packed L, later the D tiles
+    __shared__ cx<T> sL[NP]; // the packed factor
     const int lane = threadIdx.x, kr = lane >> 4, cc = lane & 15;
     const int64_t w = blockIdx.x;
     if (w >= total)
@@ -1221,38 +1398,18 @@ __global__ __launch_bounds__(64, 2) void k_back_mf(const Seg* __restrict__ segs,
     const cx<T>* P = W + s.oP + t * mm;
     const cx<T>* Q = W + s.oQ + t * mm;
     const cx<T>* g = W + s.og + t * mk;
-    {
-        // packed L: a lane's NE elements loaded together (lanes past the end
-        // load and store the last one), one round trip
-        constexpr int NE = (NP + 63) / 64;
-        const int np = m * (m + 1) / 2;
-        cx<T> lv[NE];
-#pragma unroll
-        for (int q = 0; q < NE; ++q)
-            lv[q] = L[min(lane + 64 * q, np - 1)];
-#pragma unroll
-        for (int q = 0; q < NE; ++q)
-            sL[min(lane + 64 * q, np - 1)] = lv[q];
-    }
-    __syncthreads();
-    // left operands: (L_10^H)[i][u] = conj(L[16 + u][i]), then (D_I^H)[i][u] =
-    // conj(D_I[u][i])
-    cx<T> aLh[4];
+    packed_load<T, MT>(sL, L, m);
+    // left operands (L_10^H)[i][u] = conj(L[16 + u][i]) and D_I^H
+    cx<T> aLh[4], aDh[S][4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int u = 16 + MF<T>::row(kr, v);
         const cx<T> a = (S == 2 && u < m) ? sL[u * (u + 1) / 2 + cc] : czero<T>();
         aLh[v] = cx<T>{a.r, -a.i};
     }
-    inverse_tiles_lds<T, S>(sL, m);
-    cx<T> aDh[S][4];
 #pragma unroll
     for (int I = 0; I < S; ++I)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const cx<T> a = sL[I * 256 + MF<T>::row(kr, v) * 16 + cc];
-            aDh[I][v] = cx<T>{a.r, -a.i};
-        }
+        tile_operand<T, true>(sL, I, m, aDh[I]);
 #pragma unroll 1
     for (int c0 = 0; c0 < k; c0 += 16) {
         const int cw = min(16, k - c0);
