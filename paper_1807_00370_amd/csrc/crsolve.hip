@@ -30,6 +30,7 @@
 #include "../../include/crsolve.h"
 #include "kernels.hpp"
 #include "kernels_fast.hpp"
+#include "kernels_small.hpp"
 #include "kernels_refine.hpp"
 #include "kernels_big.hpp"
 
@@ -267,6 +268,17 @@ struct Timed {
     }
 };
 
+// Launch of `waves` independent waves: work-groups of four, or of one where
+// that spreads a level with few blocks over more CUs.
+struct Shape {
+    unsigned grid, nthr;
+};
+Shape small_shape(int64_t waves)
+{
+    const int per = waves >= 2048 ? 4 : 1;
+    return Shape{(unsigned)((waves + per - 1) / per), 64u * per};
+}
+
 unsigned grid_of(int64_t total) { return (unsigned)std::min<int64_t>(total, kMaxGrid); }
 
 // Kernel dispatch per block-size class MT, element type T, level-input
@@ -287,7 +299,8 @@ struct Disp {
                                (const EI*)inB, (const EI*)iny, (cx<T>*)W, flags, mat, rhs);
         } else if constexpr (MT > 32) { // blocks above 32 run the tiled kernels
         } else if (variant == 0) {
-            hipLaunchKernelGGL((crs::k_elim_w<T, MT, EI>), dim3((unsigned)L.total), dim3(64), 0, st,
+            const Shape g = small_shape((L.total * 4 * MT + 63) / 64);
+            hipLaunchKernelGGL((crs::k_elim_s<T, MT, EI>), dim3(g.grid), dim3(g.nthr), 0, st,
                                segs + L.seg0, L.nseg, L.total, (const EI*)inA,
                                (const EI*)inB, (const EI*)iny, (cx<T>*)W, flags, mat, rhs);
         } else {
@@ -306,6 +319,11 @@ struct Disp {
             hipLaunchKernelGGL((crs::k_reduce_m<T, (MT == 16 || MT == 32) ? MT : 16, EI>), dim3((unsigned)L.total), dim3(64), 0, st,
                                segs + L.seg0, L.nseg, L.total, (const EI*)inA,
                                (const EI*)iny, (cx<T>*)W, flags, mat, rhs);
+        } else if (MT <= 8 && variant == 0) {
+            const Shape g = small_shape((L.total * MT + 7) / 8);
+            hipLaunchKernelGGL((crs::k_reduce_s<T, MT <= 8 ? MT : 8, EI>), dim3(g.grid), dim3(g.nthr), 0, st,
+                               segs + L.seg0, L.nseg, L.total, (const EI*)inA,
+                               (const EI*)iny, (cx<T>*)W, flags, mat, rhs);
         } else if (MT == 64) {
             hipLaunchKernelGGL((crs::k_reduce_t<T, 64, EI>), dim3((unsigned)L.total), dim3(64), 0, st,
                                segs + L.seg0, L.nseg, L.total, (const EI*)inA,
@@ -319,13 +337,24 @@ struct Disp {
     template <int MT>
     static void back(const Launch& L, const Seg* segs, const void* W, void* X,
                      const unsigned long long* flags, hipStream_t st, int variant, void* U,
-                     int upd)
+                     int upd, int kmax)
     {
         if constexpr (MT == 16 || MT == 32) {
             hipLaunchKernelGGL((crs::k_back_mf<T, MT>), dim3((unsigned)L.total), dim3(64), 0, st,
                                segs + L.seg0, L.nseg, L.total, (const cx<T>*)W, (cx<T>*)X, flags,
                                (cx<double>*)U, upd);
-        } else if constexpr (MT <= 32) { // blocks above 32 run the tiled kernels
+        } else if constexpr (MT > 32) { // blocks above 32 run the tiled kernels
+        } else if (variant == 0) {
+            // right-hand-side columns side by side, as many as a wave has
+            // lanes for one block
+            int cs = 0;
+            while ((1 << cs) < kmax && (MT << cs) < 64)
+                ++cs;
+            const Shape g = small_shape((((L.total * MT) << cs) + 63) / 64);
+            hipLaunchKernelGGL((crs::k_back_s<T, MT>), dim3(g.grid), dim3(g.nthr), 0, st, segs + L.seg0,
+                               L.nseg, L.total, cs, (const cx<T>*)W, (cx<T>*)X, flags,
+                               (cx<double>*)U, upd);
+        } else {
             constexpr int PW = 32;
             hipLaunchKernelGGL((crs::k_back<T, MT, kNT, PW>), dim3(grid_of(L.total)), dim3(kNT), 0,
                                st, segs + L.seg0, L.nseg, L.total, (const cx<T>*)W, (cx<T>*)X,
@@ -558,7 +587,10 @@ void run_back(const Ctx& c, const Launch& L, void* x, int upd)
         return;
     }
     const int v = c.p->var[2][L.cls][L.f64];
-#define CALL(MT) Disp<T>::template back<MT>(L, c.dsegs, c.ws, X, c.flags, c.st, v, x, u)
+    int kmax = 1;
+    for (int i = L.seg0; i < L.seg0 + L.nseg; ++i)
+        kmax = std::max(kmax, c.p->segs[i].k);
+#define CALL(MT) Disp<T>::template back<MT>(L, c.dsegs, c.ws, X, c.flags, c.st, v, x, u, kmax)
     CRS_BY_CLASS(L.cls, CALL)
 #undef CALL
 }

@@ -1,13 +1,8 @@
-// One-wave kernels of a reduction level for block sizes up to 32 (elimination,
+// One-wave kernels of a reduction level for block sizes 9 to 32 (elimination,
 // back substitution) and up to 64 (reduced-system products).  Same
 // arithmetic and outputs as the work-group kernels in kernels.hpp; the
 // difference is the mapping onto a single wave64:
 //
-//   k_elim_w    Cholesky of A_p on a packed lower triangle in LDS, then the
-//               forward substitutions L \ [B_p^H | B_{p-d} | y_p] with one
-//               lane per right-hand-side column, the column held in
-//               registers and L read by broadcast from LDS -- no work-group
-//               barriers inside the substitution.
 //   k_reduce_m  the products P^H P, Q^H Q, P^H Q, P^H g, Q^H g of Eq.
 //               (Formulas) on MFMA (16x16x4, real-pair 4-multiply complex
 //               form), operands loaded from HBM straight into the MFMA lane
@@ -47,15 +42,6 @@ struct MF<float> {
     }
     static __device__ __forceinline__ int row(int kr, int v) { return 4 * kr + v; }
 };
-
-// Waves per SIMD to ask the register allocator for when a column of MT
-// complex values lives in registers (MT * sizeof(T) / 2 VGPRs) next to the
-// operands of the substitution.
-template <class T, int MT>
-constexpr int col_waves()
-{
-    return (512 / (MT * (int)sizeof(T) / 2 + 96)) > 8 ? 8 : (512 / (MT * (int)sizeof(T) / 2 + 96));
-}
 
 template <class T>
 __device__ __forceinline__ cx<T> czero()
@@ -568,181 +554,6 @@ __device__ __forceinline__ void packed_load(cx<T>* sL, const cx<T>* __restrict__
     for (int q = 0; q < NE; ++q)
         sL[min(lane + 64 * q, np - 1)] = x[q];
     wave_lds_sync();
-}
-
-// ----------------------------------------------------------------- k_elim_w
-
-template <class T, int MT, class EI = cx<T>>
-__global__ __launch_bounds__(64, (col_waves<T, MT>())) void k_elim_w(const Seg* __restrict__ segs, int nseg,
-                                               int64_t total, const EI* __restrict__ inA,
-                                               const EI* __restrict__ inB,
-                                               const EI* __restrict__ iny,
-                                               cx<T>* __restrict__ W,
-                                               unsigned long long* __restrict__ flags,
-                                               int with_mat, int with_rhs)
-{
-    static_assert(MT <= 32, "register-resident columns");
-    constexpr int NP = MT * (MT + 1) / 2;
-    constexpr int CH = MT < 8 ? MT : 8; // columns of B_p staged per chunk
-    constexpr int CHN = MT / CH;
-    __shared__ cx<T> sL[NP];
-    __shared__ T sInv[MT];
-    __shared__ cx<T> sT[MT * (CH + 1)];
-    __shared__ int sFail;
-    const int lane = threadIdx.x;
-
-    {
-        const int64_t w = blockIdx.x;
-        if (w >= total)
-            return;
-        const Seg& s = segs[find_seg(segs, nseg, w)];
-        const int64_t t = w - s.w0;
-        const int p = s.e0 + (int)t * s.es;
-        const int m = s.m, k = s.k, d = s.d;
-        const int64_t mm = (int64_t)m * m, mk = (int64_t)m * k;
-        const int np = m * (m + 1) / 2;
-        const bool hasPrev = p - d >= 0, hasNext = p + d < s.n;
-        if ((flags[s.sys] >> 40) < (unsigned long long)s.level)
-            return;
-        cx<T>* Lg = W + s.oL + t * mm;
-        __syncthreads();
-        if (with_mat) {
-            const EI* Ap = inA + s.oA + (int64_t)p * mm;
-            for (int e = lane; e < np; e += 64) {
-                const int r = tri_row(e), c = e - r * (r + 1) / 2;
-                sL[e] = cvt<T>(Ap[r * m + c]);
-            }
-            __syncthreads();
-            // left-looking Cholesky: lane r < m keeps row r in registers; at
-            // step c every row forms its dot product with row c of L (read by
-            // broadcast from LDS), lane c's result gives the pivot, rows
-            // below it get L[r][c], and column c is published to LDS
-            cx<T> a[MT];
-            const int rl = lane < m ? lane : 0;
-#pragma unroll
-            for (int u = 0; u < MT; ++u)
-                a[u] = (u <= rl) ? sL[rl * (rl + 1) / 2 + u] : czero<T>();
-            __syncthreads();
-            bool fail = false;
-#pragma unroll
-            for (int c = 0; c < MT; ++c) {
-                if (c < m) {
-                    cx<T> s0 = czero<T>(), s1 = czero<T>();
-#pragma unroll
-                    for (int u = 0; u + 1 < c; u += 2) {
-                        msub_cb(s0, a[u], sL[c * (c + 1) / 2 + u]);
-                        msub_cb(s1, a[u + 1], sL[c * (c + 1) / 2 + u + 1]);
-                    }
-                    if (c & 1)
-                        msub_cb(s0, a[c - 1], sL[c * (c + 1) / 2 + c - 1]);
-                    // s = -(sum_u L[r][u] conj(L[c][u])); the pivot is lane c's
-                    const cx<T> v{a[c].r + s0.r + s1.r, a[c].i + s0.i + s1.i};
-                    const T dg = __shfl(v.r, c);
-                    const T inv = rsqrt_nr(dg);
-                    const T sq = dg * inv;
-                    fail |= !(dg > T(0));
-                    if (lane == c)
-                        a[c] = cx<T>{sq, inv}; // inverse pivot kept in the imaginary slot
-                    else
-                        a[c] = cx<T>{v.r * inv, v.i * inv};
-                    if (lane >= c && lane < m)
-                        sL[lane * (lane + 1) / 2 + c] = a[c];
-                    if (lane == 0)
-                        sInv[c] = inv;
-                    __syncthreads();
-                }
-                // keep the next step's loads from being hoisted (register pressure)
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (lane == 0)
-                sFail = fail;
-            if (lane == 0 && sFail)
-                atomicMin(&flags[s.sys], fail_key(s.level, s.ob0 + s.obs * p));
-            for (int e = lane; e < np; e += 64)
-                Lg[e] = sL[e];
-        } else {
-            for (int e = lane; e < np; e += 64)
-                sL[e] = Lg[e];
-            __syncthreads();
-            for (int c = lane; c < m; c += 64)
-                sInv[c] = sL[c * (c + 1) / 2 + c].i;
-        }
-        __syncthreads();
-
-        // forward substitutions, one lane per column of [B_p^H | B_{p-d} | y_p]
-        const int nP = (with_mat && hasNext) ? m : 0;
-        const int nQ = (with_mat && hasPrev) ? m : 0;
-        const int nY = with_rhs ? k : 0;
-        const int ncol = nP + nQ + nY;
-        const EI* Bp = inB + s.oB + (int64_t)p * mm;
-        const EI* Bq = inB + s.oB + (int64_t)(p - d) * mm;
-        const EI* yp = iny + s.oy + (int64_t)p * mk;
-        for (int vc0 = 0; vc0 < ncol; vc0 += 64) {
-            const int vc = vc0 + lane;
-            const bool act = vc < ncol;
-            const int src = vc < nP ? 0 : (vc < nP + nQ ? 1 : 2);
-            const int col = src == 0 ? vc : (src == 1 ? vc - nP : vc - nP - nQ);
-            cx<T> x[MT];
-#pragma unroll
-            for (int r = 0; r < MT; ++r)
-                x[r] = czero<T>();
-            if (vc0 == 0 && nP > 0) {
-                // column col of B_p^H is the conjugate of row col of B_p: stage
-                // CH columns of B_p at a time (coalesced rows), then each lane
-                // picks its row
-#pragma unroll
-                for (int ch = 0; ch < CHN; ++ch) {
-                    __syncthreads();
-                    for (int e = lane; e < m * CH; e += 64) {
-                        const int row = e / CH, j = e % CH, c2 = ch * CH + j;
-                        sT[row * (CH + 1) + j] = c2 < m ? cvt<T>(Bp[row * m + c2]) : czero<T>();
-                    }
-                    __syncthreads();
-                    if (src == 0) {
-#pragma unroll
-                        for (int j = 0; j < CH; ++j) {
-                            const cx<T> v = sT[col * (CH + 1) + j];
-                            x[ch * CH + j] = cx<T>{v.r, -v.i};
-                        }
-                    }
-                }
-            }
-            if (act && src == 1) {
-#pragma unroll
-                for (int r = 0; r < MT; ++r)
-                    if (r < m)
-                        x[r] = cvt<T>(Bq[r * m + col]);
-            } else if (act && src == 2) {
-#pragma unroll
-                for (int r = 0; r < MT; ++r)
-                    if (r < m)
-                        x[r] = cvt<T>(yp[r * k + col]);
-            }
-            // forward substitution, L by broadcast from LDS; each row's sum
-            // runs on four independent chains
-#pragma unroll
-            for (int r = 0; r < MT; ++r) {
-                if (r < m) {
-                    cx<T> v[4] = {x[r], czero<T>(), czero<T>(), czero<T>()};
-#pragma unroll
-                    for (int u = 0; u < r; ++u)
-                        msub(v[u & 3], sL[r * (r + 1) / 2 + u], x[u]);
-                    const T iv = sInv[r];
-                    x[r] = cx<T>{((v[0].r + v[1].r) + (v[2].r + v[3].r)) * iv,
-                                 ((v[0].i + v[1].i) + (v[2].i + v[3].i)) * iv};
-                }
-            }
-            if (act) {
-                cx<T>* out = src == 0 ? W + s.oP + t * mm
-                                      : (src == 1 ? W + s.oQ + t * mm : W + s.og + t * mk);
-                const int ld = src == 2 ? k : m;
-#pragma unroll
-                for (int r = 0; r < MT; ++r)
-                    if (r < m)
-                        out[r * ld + col] = x[r];
-            }
-        }
-    }
 }
 
 // ---------------------------------------------------------------- k_elim_mf
