@@ -421,9 +421,9 @@ BigDims big_dims(const crsolve_plan* p, const Launch& L)
     return b;
 }
 
-// FP64 tiled forward substitutions of launches with at least this many blocks
-// run one wave per strip (k_trsm_strip); fewer blocks, or FP32, take the
-// work-group form with its shorter chain and shared L tiles.
+// k_trsm_strip (FP64 complex blocks above 128) keeps eight contraction steps
+// of loads in flight in launches of fewer blocks than this, which are bound by
+// one strip's chain, and four in others (at 64 blocks 345 -> 325 us).
 constexpr int64_t kTrsmStripBlocks = 256;
 
 // Tiled Cholesky launches of at most this many blocks (one per CU) run
@@ -468,34 +468,32 @@ void run_elim(const Ctx& c, const Launch& L, const void* A, const void* B, const
         }
         const int ns = (mat ? 2 * b.S : 0) + (rhs ? b.K16 : 0);
         if (ns > 0) {
-            constexpr int NC = crs::trsm_strips<T>();
-            const int ngrp = (ns + NC - 1) / NC;
             Timed tm(c.p, KID_TRSM, c.st, L.cls, L.f64);
-            if (sizeof(T) == 8 && L.total >= kTrsmStripBlocks && L.cls == kBig)
-                // the real form's single-MFMA steps take the deeper prefetch
-                // (Poisson real form k_trsm 13.5 -> 13.2 ms; the complex form
-                // measured slower with it, 14.0 -> 14.7 ms)
-                hipLaunchKernelGGL((crs::k_trsm_strip<T, EI, RE, 1, RE ? 8 : 0>), dim3(grid8(L.total * ns)),
-                                   dim3(64), 0, c.st, c.dsegs + L.seg0, L.nseg, L.total, ns, mat, rhs,
+            auto go = [&](auto kernel) {
+                // the block's strips dealt evenly over groups of at most four
+                const int ngrp = (ns + 3) / 4, per = (ns + ngrp - 1) / ngrp;
+                hipLaunchKernelGGL(kernel, dim3(grid8(L.total * ngrp)), dim3(256), 0, c.st,
+                                   c.dsegs + L.seg0, L.nseg, L.total, ngrp, per, mat, rhs,
                                    (const EI*)inB, (const EI*)iny, (cx<T>*)c.ws, c.flags);
-            else if (sizeof(T) == 8 && L.cls == kBig)
-                // few blocks: every strip's chain of loads in flight eight
-                // contraction steps deep
-                hipLaunchKernelGGL((crs::k_trsm_strip<T, EI, RE, 1, 8>), dim3(grid8(L.total * ns)), dim3(64), 0,
-                                   c.st, c.dsegs + L.seg0, L.nseg, L.total, ns, mat, rhs,
-                                   (const EI*)inB, (const EI*)iny, (cx<T>*)c.ws, c.flags);
-            else if (sizeof(T) == 8 && L.total >= kTrsmStripBlocks) {
-                // blocks of 33..64: two strips per wave, ceil(S / 2) items per
-                // B and ceil(K16 / 2) of y
-                const int ni = (mat ? 2 * ((b.S + 1) / 2) : 0) + (rhs ? (b.K16 + 1) / 2 : 0);
-                hipLaunchKernelGGL((crs::k_trsm_strip<T, EI, RE, 2>), dim3(grid8(L.total * ni)), dim3(64), 0,
-                                   c.st, c.dsegs + L.seg0, L.nseg, L.total, ni, mat, rhs,
-                                   (const EI*)inB, (const EI*)iny, (cx<T>*)c.ws, c.flags);
-            }
-            else
-                hipLaunchKernelGGL((crs::k_trsm_big<T, EI, RE>), dim3(grid8(L.total * ngrp)), dim3(64 * b.S),
-                                   0, c.st, c.dsegs + L.seg0, L.nseg, L.total, ngrp, mat, rhs,
-                                   (const EI*)inB, (const EI*)iny, (cx<T>*)c.ws, c.flags);
+            };
+            if (b.S <= 4)
+                go(crs::k_trsm_reg<T, 4, EI, RE>);
+            else if (b.S <= 8)
+                go(crs::k_trsm_reg<T, 8, EI, RE>);
+            else if constexpr (sizeof(T) == 8 && !RE) {
+                // FP64 complex above 128: the strip's accumulators would take
+                // the whole register file of a SIMD (see k_trsm_strip)
+                auto strip = [&](auto kernel) {
+                    hipLaunchKernelGGL(kernel, dim3(grid8(L.total * ns)), dim3(64), 0, c.st,
+                                       c.dsegs + L.seg0, L.nseg, L.total, ns, mat, rhs,
+                                       (const EI*)inB, (const EI*)iny, (cx<T>*)c.ws, c.flags);
+                };
+                if (L.total >= kTrsmStripBlocks)
+                    strip(crs::k_trsm_strip<T, EI, 4>);
+                else
+                    strip(crs::k_trsm_strip<T, EI, 8>);
+            } else
+                go(crs::k_trsm_reg<T, 16, EI, RE>);
         }
         return;
     }

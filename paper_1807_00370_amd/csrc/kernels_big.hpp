@@ -10,11 +10,14 @@
 //                 diagonal tile is factored in registers (one row per lane)
 //                 and its inverse D_I = L_II^{-1} is kept for the
 //                 substitutions; the tiles below become S_R D_I^H.
-//   k_trsm_big    one work-group per (eliminated block, group of 16-column
-//                 strips of [B_p^H | B_{p-d} | y_p]), one wave per row tile:
-//                 blocked forward substitution
+//   k_trsm_reg    one wave per (eliminated block, 16-column strip of
+//                 [B_p^H | B_{p-d} | y_p]), four strips of a block per
+//                 work-group: blocked forward substitution
 //                 X_I = D_I (G_I - L[I][<I] X_{<I}), the Section 4 recipe
-//                 L \ G for the three operands of Eq. (Formulas).
+//                 L \ G for the three operands of Eq. (Formulas), the strip
+//                 in registers and L staged in LDS column by column.
+//   k_trsm_strip  the same, one wave per work-group with the finished rows
+//                 re-read, for FP64 complex blocks above 128.
 //   k_reduce_big  one wave per (kept block, 16 or 32 wide tile) of the reduced
 //                 system A' = A_q - P_l^H P_l - Q_r^H Q_r (lower triangle),
 //                 B' = -P_r^H Q_r, y' = y_q - P_l^H g_l - Q_r^H g_r; with
@@ -587,41 +590,66 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
         atomicMin(&flags[s.sys], fail_key(s.level, s.ob0 + s.obs * p));
 }
 
-// -------------------------------------------------------------- k_trsm_big
+// -------------------------------------------------------------- k_trsm_reg
 
-// Strips per work-group of the tiled forward substitution: every L tile a
-// wave loads serves this many 16-column strips.
+// Forward substitutions L \ [B_p^H | B_{p-d} | y_p] of the tiled blocks: a
+// work-group of four waves per (block, four 16-column strips), one strip per
+// wave with all its row tiles W_I (at most SM) in accumulator registers from
+// the first load of the right-hand side to the store of the result.
+// Right-looking over the columns J of L: X_J = D_J W_J (the accumulator is the
+// right operand, see the note in k_elim_mf), then W_I -= L_IJ X_J for every
+// I > J -- independent accumulators, so the matrix unit never waits for its
+// own result.  Column J of L and D_J, the left operands of all four strips,
+// come through LDS once per work-group, column J + 1 being fetched (into
+// registers, then the other LDS buffer) while J is used: one barrier per
+// column.  Tiles are stored 16 x 17 so that the operand reads (16 rows, four
+// columns) fall on different banks.
+//
+// FP64 MFMA is what bounds it: 16 (four-multiplication form; real data 4)
+// instructions of 64 cycles per 16 x 16 product against four LDS reads and a
+// quarter of a tile from L2.  Against one wave per strip (or two) that reads
+// its finished rows back from memory, N = 4096, m = 256 real: 13.2 -> 5.7 ms
+// per solve; FP64 complex m = 64 with k = 64, factor and adjoint: 2.54 -> 2.05
+// ms.  Eight waves per group halve the passes over L above 128 and were
+// slower all the same (6.8 ms): one barrier then holds up eight strips.
+template <class T, bool RE>
+struct trsm_el { // operand element in LDS: real data keeps the real part only
+    using type = cx<T>;
+    static __device__ __forceinline__ type to(const cx<T> v) { return v; }
+    static __device__ __forceinline__ cx<T> from(const type v) { return v; }
+};
 template <class T>
-constexpr int trsm_strips()
+struct trsm_el<T, true> {
+    using type = T;
+    static __device__ __forceinline__ type to(const cx<T> v) { return v.r; }
+    static __device__ __forceinline__ cx<T> from(const type v) { return cx<T>{v, T(0)}; }
+};
+
+// Waves per SIMD that the accumulators of SM row tiles (and the column in
+// flight) leave room for.
+template <class T, bool RE, int SM>
+constexpr int trsm_waves()
 {
-    return sizeof(T) == 8 ? 2 : 4;
+    return SM == 16 ? (RE || sizeof(T) == 4 ? 2 : 1) : SM == 8 ? (RE || sizeof(T) == 4 ? 3 : 2)
+                                                               : (RE || sizeof(T) == 4 ? 4 : 3);
 }
 
-// One work-group per (eliminated block, group of NC = trsm_strips<T>()
-// 16-column strips of [B_p^H | B_{p-d} | y_p]), one wave per 16-row tile I
-// (blockDim = 64 x the largest tile count of the launch).  Strip u of a block
-// is a column strip of B_p^H for u < S, of B_{p-d} for u < 2 S (with_mat), of
-// y_p after them (with_rhs).  Top-down over the tiles J: wave J forms
-// X_J = D_J (G_J - acc_J), the accumulator being the right operand (see the
-// note in k_elim_mf), stores it and publishes it in LDS; every wave I > J
-// then accumulates acc_I += L_IJ X_J (its operand loaded one step ahead).
-template <class T, class EI = cx<T>, bool RE = false>
-__global__ __launch_bounds__(1024) void k_trsm_big(const Seg* __restrict__ segs, int nseg,
-                                                   int64_t total, int ngrp, int with_mat,
-                                                   int with_rhs, const EI* __restrict__ inB,
-                                                   const EI* __restrict__ iny,
-                                                   cx<T>* __restrict__ W,
-                                                   const unsigned long long* __restrict__ flags)
+template <class T, int SM, class EI = cx<T>, bool RE = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trsm_waves<T, RE, SM>(), 8))) void k_trsm_reg(
+    const Seg* __restrict__ segs, int nseg, int64_t total, int ngrp, int per, int with_mat, int with_rhs,
+    const EI* __restrict__ inB, const EI* __restrict__ iny, cx<T>* __restrict__ W,
+    const unsigned long long* __restrict__ flags)
 {
     using v4 = typename MF<T>::v4;
-    constexpr int NC = trsm_strips<T>();
-    __shared__ cx<T> sx[NC][256]; // X_J of each strip, row-major 16 x 16
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
+    using EL = trsm_el<T, RE>;
+    constexpr int TS = 16 * 17; // a tile in LDS
+    __shared__ typename EL::type sC[2][SM * TS]; // D_J, then L_IJ of I > J
+    const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, kr = lane >> 4, cc = lane & 15;
     const int64_t li = xcd_item();
     const int64_t w = li / ngrp;
-    const int grp = (int)(li - w * ngrp);
     if (w >= total)
         return;
+    const int grp = (int)(li - w * ngrp);
     const Seg& s = segs[find_seg(segs, nseg, w)];
     const int64_t t = w - s.w0;
     const int p = s.e0 + (int)t * s.es;
@@ -629,152 +657,155 @@ __global__ __launch_bounds__(1024) void k_trsm_big(const Seg* __restrict__ segs,
     if ((flags[s.sys] >> 40) < (unsigned long long)s.level)
         return;
     const int64_t mm = (int64_t)m * m, mk = (int64_t)m * k;
-    const bool hasPrev = p - d >= 0, hasNext = p + d < s.n;
-    const int nmat = with_mat ? 2 * S : 0;
-    const int nstrip = nmat + (with_rhs ? (k + 15) / 16 : 0);
-    // per strip slot b: element (r, c) of the right-hand side is
-    // G[b][r * gr[b] + c * gc[b]] (conjugated for B_p^H), the solution goes
-    // to out[b][r * ld[b] + c], columns c0[b] .. c0[b] + nc[b] - 1
-    const EI* G[NC];
-    cx<T>* out[NC];
-    int gr[NC], gc[NC], ld[NC], c0[NC], nc[NC];
-    bool cj[NC], on[NC];
-    bool any = false;
-#pragma unroll
-    for (int b = 0; b < NC; ++b) {
-        const int u = grp * NC + b;
-        int src = 2, cu = u - nmat;
-        if (u < nmat) {
-            src = u < S ? 0 : 1;
-            cu = u < S ? u : u - S;
-        }
-        on[b] = u < nstrip && (src == 0 ? hasNext : (src == 1 ? hasPrev : true));
-        c0[b] = 16 * cu;
-        const int ncol = src == 2 ? k : m;
-        nc[b] = on[b] ? min(16, ncol - c0[b]) : 0;
-        on[b] = on[b] && nc[b] > 0;
-        cj[b] = src == 0;
-        if (src == 0) {
-            G[b] = inB + s.oB + (int64_t)p * mm;
-            gr[b] = 1;
-            gc[b] = m;
-            out[b] = W + s.oP + t * mm;
-            ld[b] = m;
-        } else if (src == 1) {
-            G[b] = inB + s.oB + (int64_t)(p - d) * mm;
-            gr[b] = m;
-            gc[b] = 1;
-            out[b] = W + s.oQ + t * mm;
-            ld[b] = m;
-        } else {
-            G[b] = iny + s.oy + (int64_t)p * mk;
-            gr[b] = k;
-            gc[b] = 1;
-            out[b] = W + s.og + t * mk;
-            ld[b] = k;
-        }
-        any |= on[b];
-    }
-    if (!any)
+    // the block's strips: S of B_p^H and S of B_{p-d} where it has those
+    // neighbours, then those of y_p; this wave's is 4 grp + wv
+    const int nP = with_mat && p + d < s.n ? S : 0, nQ = with_mat && p - d >= 0 ? S : 0;
+    const int nst = nP + nQ + (with_rhs ? (k + 15) >> 4 : 0);
+    if (per * grp >= nst)
         return;
+    const int u = per * grp + wv;
+    const bool on = wv < per && u < nst;
+    const int src = !on || u < nP ? 0 : u < nP + nQ ? 1 : 2;
+    const int c0 = 16 * (src == 0 ? u : src == 1 ? u - nP : u - nP - nQ);
+    const int nc = on ? min(16, (src == 2 ? k : m) - c0) : 0;
     const cx<T>* Lg = W + s.oL + t * mm;
     const cx<T>* Dg = W + s.oD + t * (int64_t)S * 256;
-    const bool own = wv < S;
-    const int r0 = 16 * wv;
-    // D_I operand of this wave's tile and its right-hand sides (accumulator layout)
-    cx<T> aD[4];
+    // thread tid moves element (tid / 16, tid % 16) of every tile of a column
+    const int er = tid >> 4, ec = tid & 15;
+    cx<T> cn[SM];
+    auto fetch = [&](int J) {
+        cn[0] = Dg[J * 256 + tid];
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-        aD[v] = own ? Dg[wv * 256 + cc * 16 + MF<T>::row(kr, v)] : czero<T>();
-    v4 ar[NC], ai[NC];
-#pragma unroll
-    for (int b = 0; b < NC; ++b)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int r = r0 + MF<T>::row(kr, v);
-            cx<T> x = czero<T>();
-            if (own && on[b] && r < m && cc < nc[b])
-                x = cvt<T>(G[b][r * gr[b] + (c0[b] + cc) * gc[b]]);
-            ar[b][v] = x.r;
-            ai[b][v] = cj[b] ? -x.i : x.i;
-        }
-    // operand of the update at step J: A(i, t) = L[r0 + i][16 J + t]
-    auto load_l = [&](int J, cx<T>(&a)[4]) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            a[q] = (own && wv > J && r0 + cc < m) ? Lg[(int64_t)(r0 + cc) * m + 16 * J + 4 * q + kr]
-                                                  : czero<T>();
+        for (int q = 1; q < SM; ++q) {
+            cn[q] = czero<T>();
+            if (16 * (J + q) < m) // uniform
+                cn[q] = Lg[(int64_t)min(16 * (J + q) + er, m - 1) * m + min(16 * J + ec, m - 1)];
         }
     };
-    cx<T> an[4];
-    load_l(0, an);
-    for (int J = 0; J < S; ++J) {
-        cx<T> a[4];
+    auto put = [&](int J) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            a[q] = an[q];
-        if (J + 1 < S)
-            load_l(J + 1, an);
-        if (wv == J) {
-#pragma unroll
-            for (int b = 0; b < NC; ++b) {
-                if (!on[b])
-                    continue;
-                // X_J = D_J acc (acc holds G_J - sum of the updates)
-                v4 xr = {0, 0, 0, 0}, xi = {0, 0, 0, 0};
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const cx<T> q = aD[v];
-                    xr = MF<T>::mma(q.r, ar[b][v], xr);
-                    if constexpr (!RE) {
-                        xr = MF<T>::mma(-q.i, ai[b][v], xr);
-                        xi = MF<T>::mma(q.r, ai[b][v], xi);
-                        xi = MF<T>::mma(q.i, ar[b][v], xi);
-                    }
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int rr = MF<T>::row(kr, v), r = r0 + rr;
-                    sx[b][rr * 16 + cc] = cx<T>{xr[v], xi[v]};
-                    if (r < m && cc < nc[b])
-                        out[b][(int64_t)r * ld[b] + c0[b] + cc] = cx<T>{xr[v], xi[v]};
-                }
-            }
+        for (int q = 0; q < SM; ++q) {
+            const bool ok = q == 0 || 16 * (J + q) + er < m;
+            if (q == 0 || 16 * (J + q) < m)
+                sC[J & 1][q * TS + er * 17 + ec] =
+                    EL::to(cx<T>{ok ? cn[q].r : T(0), ok ? cn[q].i : T(0)});
         }
-        __syncthreads();
-        if (own && wv > J) {
+    };
+    fetch(0);
+    // right-hand side: element (r, c) is G[r * gr + (c0 + c) * gc], conjugated
+    // for B_p^H
+    const EI* G = src == 2 ? iny + s.oy + (int64_t)p * mk
+                           : inB + s.oB + (int64_t)(src == 0 ? p : p - d) * mm;
+    const int gr = src == 0 ? 1 : src == 1 ? m : k, gc = src == 0 ? m : 1;
+    const int ldo = src == 2 ? k : m;
+    cx<T>* out = W + (src == 0 ? s.oP : src == 1 ? s.oQ : s.og) + t * (src == 2 ? mk : mm) + c0 + cc;
+    // every element set on every path: hipcc 7.2 has dropped the real part of a
+    // value that only some paths to its use defined
+    v4 wr[SM], wi[RE ? 1 : SM];
 #pragma unroll
-            for (int b = 0; b < NC; ++b) {
-                if (!on[b])
-                    continue;
-                // acc_I -= L_IJ X_J: contraction step q pairs t = 4 q + kr
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const cx<T> x = sx[b][(4 * q + kr) * 16 + cc];
-                    ar[b] = MF<T>::mma(-a[q].r, x.r, ar[b]);
-                    if constexpr (!RE) {
-                        ar[b] = MF<T>::mma(a[q].i, x.i, ar[b]);
-                        ai[b] = MF<T>::mma(-a[q].r, x.i, ai[b]);
-                        ai[b] = MF<T>::mma(-a[q].i, x.r, ai[b]);
-                    }
-                }
-            }
-        }
-        __syncthreads();
+    for (int I = 0; I < SM; ++I) {
+        wr[I] = v4{0, 0, 0, 0};
+        if (!RE)
+            wi[I] = v4{0, 0, 0, 0};
     }
+    if (nc > 0) { // uniform within the wave
+        const EI* Gc = G + (c0 + min(cc, nc - 1)) * gc;
+        const bool okc = cc < nc;
+#pragma unroll
+        for (int I = 0; I < SM; ++I)
+            if (16 * I < m) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int r = 16 * I + MF<T>::row(kr, v);
+                    const cx<T> x = cvt<T>(Gc[min(r, m - 1) * gr]);
+                    const bool ok = okc && r < m;
+                    wr[I][v] = ok ? x.r : T(0);
+                    if constexpr (!RE)
+                        wi[I][v] = ok ? (src == 0 ? -x.i : x.i) : T(0);
+                }
+            }
+    }
+    put(0);
+    __syncthreads();
+    // the columns by recursion: the compiler leaves a loop of this size rolled,
+    // and the accumulators need constant indices
+    auto column = [&](auto self, auto Jc) {
+        constexpr int J = decltype(Jc)::value;
+        if (J >= S)
+            return;
+        const typename EL::type* col = sC[J & 1] + cc * 17;
+        if (J + 1 < S)
+            fetch(J + 1);
+        cx<T> a[4], an[4];
+        v4 xr = {0, 0, 0, 0}, xi = {0, 0, 0, 0}, nr, ni;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            an[v] = czero<T>();
+        auto operand = [&](int q, cx<T>(&x)[4]) { // left operand of tile q of the column
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[v] = EL::from(col[q * TS + MF<T>::row(kr, v)]);
+        };
+        if (nc > 0) {
+            operand(0, a);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                xr = MF<T>::mma(a[v].r, wr[J][v], xr);
+                if constexpr (!RE) {
+                    xi = MF<T>::mma(a[v].r, wi[J][v], xi);
+                    xr = MF<T>::mma(a[v].i, -wi[J][v], xr);
+                    xi = MF<T>::mma(a[v].i, wr[J][v], xi);
+                }
+            }
+        }
+        nr = -xr;
+        ni = -xi;
+        if (J + 1 < SM && nc > 0) {
+            operand(1, an);
+#pragma unroll
+            for (int I = J + 1; I < SM; ++I) {
+                if (I >= S)
+                    break;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    a[v] = an[v];
+                if (I + 1 < SM)
+                    operand(I + 1 - J, an);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    wr[I] = MF<T>::mma(a[v].r, nr[v], wr[I]);
+                    if constexpr (!RE) {
+                        wi[I] = MF<T>::mma(a[v].r, ni[v], wi[I]);
+                        wr[I] = MF<T>::mma(a[v].i, xi[v], wr[I]);
+                        wi[I] = MF<T>::mma(a[v].i, nr[v], wi[I]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int r = 16 * J + MF<T>::row(kr, v);
+            if (r < m && cc < nc)
+                out[(int64_t)r * ldo] = cx<T>{xr[v], RE ? T(0) : xi[v]};
+        }
+        if (J + 1 < S)
+            put(J + 1);
+        __syncthreads();
+        if constexpr (J + 1 < SM)
+            self(self, std::integral_constant<int, J + 1>{});
+    };
+    column(column, std::integral_constant<int, 0>{});
 }
 
-// One wave per (eliminated block, NW adjacent 16-column strips): the same
-// substitution with each wave sweeping all row tiles of its strips (no
-// barriers).  Work items of a block: with_mat gives ceil(S / NW) items of
-// columns of B_p^H, then as many of B_{p-d}, with_rhs ceil(ceil(k / 16) / NW)
-// items of y_p after them.  With NW = 2 every L tile a wave loads serves two
-// strips, which halves the L traffic through L2 and the item count (blocks of
-// 33..64; at m = 256 it measured no faster in complex and slower in real
-// form).  Used for FP64 levels with many blocks, where the work-group form's
-// idle waves would cost throughput, and with eight contraction steps per load
-// group for FP64 levels of few blocks above 64.
-template <class T, class EI = cx<T>, bool RE = false, int NW = 1, int GD = 0>
+// ------------------------------------------------------------ k_trsm_strip
+
+// One wave per (eliminated block, 16-column strip), sweeping the row tiles of
+// its strip without barriers: X_I = D_I (G_I - L_I X) with the finished rows of
+// X read back as the right operand.  Serves FP64 complex blocks above 128, for
+// which the accumulators of k_trsm_reg (256 registers of 512, and scratch)
+// leave one wave per SIMD: N = 1023, m = 200, 2.42 ms per solve here, 2.80
+// there.  GD contraction steps per load group: eight for launches of few blocks.
+template <class T, class EI, int GD>
 __global__ __launch_bounds__(64) void k_trsm_strip(const Seg* __restrict__ segs, int nseg,
                                                  int64_t total, int nstrip, int with_mat,
                                                  int with_rhs, const EI* __restrict__ inB,
@@ -796,25 +827,24 @@ __global__ __launch_bounds__(64) void k_trsm_strip(const Seg* __restrict__ segs,
     if ((flags[s.sys] >> 40) < (unsigned long long)s.level)
         return;
     const int64_t mm = (int64_t)m * m, mk = (int64_t)m * k;
-    const int SI = (S + NW - 1) / NW; // items of B_p^H (and of B_{p-d})
     int src = 2;
     if (with_mat) {
-        if (u < 2 * SI)
-            src = u < SI ? 0 : 1;
+        if (u < 2 * S)
+            src = u < S ? 0 : 1;
         else
-            u -= 2 * SI;
+            u -= 2 * S;
     }
     int c0;
     if (src == 2) {
-        c0 = 16 * NW * u;
+        c0 = 16 * u;
         if (!with_rhs || c0 >= k)
             return;
     } else {
-        c0 = 16 * NW * (src == 0 ? u : u - SI);
+        c0 = 16 * (src == 0 ? u : u - S);
         if (src == 0 ? p + d >= s.n : p - d < 0)
             return;
     }
-    const int nc = min(16 * NW, (src == 2 ? k : m) - c0);
+    const int nc = min(16, (src == 2 ? k : m) - c0);
     // element (r, c) of the right-hand side is G[r * gr + c * gc]
     const EI* G;
     int gr, gc;
@@ -838,46 +868,38 @@ __global__ __launch_bounds__(64) void k_trsm_strip(const Seg* __restrict__ segs,
     const int ldo = src == 2 ? k : m;
     const cx<T>* Lg = W + s.oL + t * mm;
     const cx<T>* Dg = W + s.oD + t * (int64_t)S * 256;
-    // two complex strips keep two contraction steps per load group in flight
-    // instead of four (the same operand registers); the real form has the
-    // registers for four.  GD > 0 sets the depth (launches of few blocks,
-    // where each wave's chain of loads, not the occupancy, sets the time).
-    constexpr int GK = GD > 0 ? GD : ((NW == 1 || RE) ? 4 : 2);
     for (int I = 0; I < S; ++I) {
         const int r0 = 16 * I;
-        Acc3<T, 1, NW, RE> acc;
+        // the accumulator starts at -G_I and ends at -w, w = G_I - L_I X: the
+        // order of k_trsm_reg, so that real data gives the same bits as there.
+        // Register v of lane (kr, cc) holds row MF::row(kr, v) of column cc
+        Acc3<T, 1, 1, false> acc;
         acc.zero();
-        wave_mm3<T, 1, NW, false, false, GK, RE>(acc, WOp<T>{Lg + (int64_t)r0 * m, m, 1, m - r0},
-                                                WOp<T>{out + c0, 1, ldo, nc}, r0);
-        // w = G_I - acc stays in the accumulator layout: register v of lane
-        // (kr, cc) holds row MF::row(kr, v) of column cc, which is the right
-        // operand of contraction step v once the left operand D_I supplies
-        // column MF::row(kr, v) of its row cc
-        Acc3<T, 1, NW, RE> x;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int r = r0 + MF<T>::row(kr, v);
+            cx<T> g = (r < m && cc < nc) ? cvt<T>(G[r * gr + (c0 + cc) * gc]) : czero<T>();
+            if (src == 0)
+                g.i = -g.i;
+            acc.t1[0][0][v] = -g.r;
+            acc.t3[0][0][v] = -(g.r + g.i);
+        }
+        wave_mm3<T, 1, 1, false, false, GD, false>(acc, WOp<T>{Lg + (int64_t)r0 * m, m, 1, m - r0},
+                                                   WOp<T>{out + c0, 1, ldo, nc}, r0);
+        // register v is the right operand of contraction step v once the left
+        // operand D_I supplies column MF::row(kr, v) of its row cc
+        Acc3<T, 1, 1, false> x;
         x.zero();
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int rr = MF<T>::row(kr, v), r = r0 + rr;
-            const cx<T> a = Dg[I * 256 + cc * 16 + rr];
-#pragma unroll
-            for (int b = 0; b < NW; ++b) {
-                const int c = 16 * b + cc;
-                cx<T> g = (r < m && c < nc) ? cvt<T>(G[r * gr + (c0 + c) * gc]) : czero<T>();
-                if (src == 0)
-                    g.i = -g.i;
-                const T br = g.r - acc.re(0, b, v), bi = g.i - acc.im(0, b, v);
-                x.step(0, b, a.r, a.i, br, bi);
-            }
+            const cx<T> a = Dg[I * 256 + cc * 16 + MF<T>::row(kr, v)];
+            x.step(0, 0, a.r, a.i, -acc.re(0, 0, v), -acc.im(0, 0, v));
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int r = r0 + MF<T>::row(kr, v);
-#pragma unroll
-            for (int b = 0; b < NW; ++b) {
-                const int c = 16 * b + cc;
-                if (r < m && c < nc)
-                    out[(int64_t)r * ldo + c0 + c] = cx<T>{x.re(0, b, v), x.im(0, b, v)};
-            }
+            if (r < m && cc < nc)
+                out[(int64_t)r * ldo + c0 + cc] = cx<T>{x.re(0, 0, v), x.im(0, 0, v)};
         }
         __syncthreads(); // the rows just stored are the next tiles' operands
     }
