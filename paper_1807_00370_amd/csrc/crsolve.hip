@@ -426,8 +426,9 @@ BigDims big_dims(const crsolve_plan* p, const Launch& L)
 // one strip's chain, and four in others (at 64 blocks 345 -> 325 us).
 constexpr int64_t kTrsmStripBlocks = 256;
 
-// Tiled Cholesky launches of at most this many blocks (one per CU) run
-// work-groups of eight waves.
+// FP64 complex Cholesky above 128: launches of at most this many blocks (one
+// per CU) run k_potrf_rl, 144 us per launch of few blocks at m = 200; 512 blocks
+// take 342 us with k_potrf_big.
 constexpr int64_t kPotrfWideBlocks = 256;
 
 // Grid of the tiled kernels: a multiple of 8 work-groups (see xcd_item).
@@ -454,17 +455,25 @@ void run_elim(const Ctx& c, const Launch& L, const void* A, const void* B, const
         const BigDims b = big_dims(c.p, L);
         if (mat) {
             Timed tm(c.p, KID_POTRF, c.st, L.cls, L.f64);
-            if (L.total <= kPotrfWideBlocks)
-                // few blocks (every tiled class): one block's chain of panels
-                // sets the time, so the diagonal steps run ahead of the
-                // trailing updates
-                hipLaunchKernelGGL((crs::k_potrf_rl<T, EI, RE>), dim3((unsigned)L.total), dim3(512), 0,
-                                   c.st, c.dsegs + L.seg0, L.nseg, L.total, (const EI*)inA,
-                                   (cx<T>*)c.ws, c.flags);
-            else
-                hipLaunchKernelGGL((crs::k_potrf_big<T, EI, RE>), dim3((unsigned)L.total), dim3(256), 0,
-                                   c.st, c.dsegs + L.seg0, L.nseg, L.total, (const EI*)inA,
-                                   (cx<T>*)c.ws, c.flags);
+            auto go = [&](auto kernel, int threads) {
+                hipLaunchKernelGGL(kernel, dim3((unsigned)L.total), dim3(threads), 0, c.st,
+                                   c.dsegs + L.seg0, L.nseg, L.total, (const EI*)inA, (cx<T>*)c.ws,
+                                   c.flags);
+            };
+            if (b.S <= 4)
+                go(crs::k_potrf_reg<T, 4, EI, RE>, 128);
+            else if (b.S <= 8)
+                go(crs::k_potrf_reg<T, 8, EI, RE>, 256);
+            else if constexpr (sizeof(T) == 8 && !RE) {
+                // FP64 complex above 128 exceeds a CU's registers.  Few blocks:
+                // one block's chain of panels sets the time, so the diagonal
+                // steps run ahead of the trailing updates
+                if (L.total <= kPotrfWideBlocks)
+                    go(crs::k_potrf_rl<T, EI>, 512);
+                else
+                    go(crs::k_potrf_big<T, EI>, 256);
+            } else
+                go(crs::k_potrf_reg<T, 16, EI, RE>, 512);
         }
         const int ns = (mat ? 2 * b.S : 0) + (rhs ? b.K16 : 0);
         if (ns > 0) {

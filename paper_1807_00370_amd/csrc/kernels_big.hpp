@@ -3,13 +3,13 @@
 // step is cut into 16 x 16 MFMA tiles whose operands stream from L2 (the
 // streaming products in the three-multiplication complex form, Acc3):
 //
-//   k_potrf_big   one work-group (four or eight waves) per eliminated
-//                 block: blocked left-looking
-//                 Cholesky L_p = chol(A_p) by 16-column panels.  The panel
-//                 update L[R][<I] L[I][<I]^H runs on MFMA, each 16 x 16
-//                 diagonal tile is factored in registers (one row per lane)
-//                 and its inverse D_I = L_II^{-1} is kept for the
-//                 substitutions; the tiles below become S_R D_I^H.
+//   k_potrf_reg   one work-group per eliminated block, the block held in its
+//                 registers: right-looking Cholesky L_p = chol(A_p) by
+//                 16-column panels.  Each 16 x 16 diagonal tile is factored
+//                 and inverted by one wave (tile_chol); its inverse
+//                 D_I = L_II^{-1} is kept for the substitutions.
+//   k_potrf_big, k_potrf_rl   the same from memory, for FP64 complex blocks
+//                 above 128 (launches of many and of few blocks).
 //   k_trsm_reg    one wave per (eliminated block, 16-column strip of
 //                 [B_p^H | B_{p-d} | y_p]), four strips of a block per
 //                 work-group: blocked forward substitution
@@ -286,7 +286,7 @@ __device__ __forceinline__ void zero_acc(typename MF<T>::v4 (&cr)[RM][RN],
 // inverted in the registers (tile_chol).  L_II goes to L (diagonal
 // {L_cc, 1 / L_cc}), D_I to Dg and to sD (leading dimension 17).  Returns
 // true on a pivot that is not > 0.
-template <class T, bool RE>
+template <class T>
 __device__ __forceinline__ bool potrf_diag_tile(cx<T>* sT, cx<T>* sD, cx<T>* __restrict__ Lg,
                                                 cx<T>* __restrict__ Dg, int m, int I)
 {
@@ -300,7 +300,7 @@ __device__ __forceinline__ bool potrf_diag_tile(cx<T>* sT, cx<T>* sD, cx<T>* __r
         if (gi >= m)
             t[v] = cx<double>{u == r ? 1.0 : 0.0, 0.0};
     }
-    const bool fail = tile_chol<T, RE>(t, l, e, m - c0);
+    const bool fail = tile_chol<T>(t, l, e, m - c0);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int u = kr + 4 * v;
@@ -315,7 +315,7 @@ __device__ __forceinline__ bool potrf_diag_tile(cx<T>* sT, cx<T>* sD, cx<T>* __r
 
 // ------------------------------------------------------------- k_potrf_big
 
-template <class T, class EI = cx<T>, bool RE = false>
+template <class T, class EI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_potrf_big(const Seg* __restrict__ segs, int nseg,
                                                    int64_t total, const EI* __restrict__ inA,
                                                    cx<T>* __restrict__ W,
@@ -347,9 +347,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
         // panel column I: S_R = A[R][I] - L[R][<I] L[I][<I]^H for R >= I (the
         // Hermitian reading of A: lower triangle of the diagonal tile only)
         for (int R = I + wv; R < S; R += nw) {
-            Acc3<T, 1, 1, RE> acc;
+            Acc3<T, 1, 1> acc;
             acc.zero();
-            wave_mm3<T, 1, 1, false, true, 4, RE>(acc, WOp<T>{Lg + (int64_t)16 * R * m, m, 1, m - 16 * R},
+            wave_mm3<T, 1, 1, false, true, 4>(acc, WOp<T>{Lg + (int64_t)16 * R * m, m, 1, m - 16 * R},
                                               WOp<T>{Lg + (int64_t)c0 * m, m, 1, m - c0}, c0);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
         __syncthreads();
         // diagonal tile: L_II and D_I (wave 0)
         if (wv == 0) {
-            const bool fail = potrf_diag_tile<T, RE>(sT, sD, Lg, Dg, m, I);
+            const bool fail = potrf_diag_tile<T>(sT, sD, Lg, Dg, m, I);
             if (lane == 0 && fail)
                 sFail = 1;
         }
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
                 sa[q] = (i < m && tc < kd) ? Lg[(int64_t)i * m + c0 + tc] : czero<T>();
                 db[q] = tc < kd ? sD[cc * 17 + tc] : czero<T>();
             }
-            Acc3<T, 1, 1, RE> acc;
+            Acc3<T, 1, 1> acc;
             acc.zero();
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 // factored) and writes every lower tile of the slot once; later panels read
 // and update the slot.  The trailing sums round once per panel: the same
 // factorization as k_potrf_big up to rounding order.
-template <class T, class EI = cx<T>, bool RE = false>
+template <class T, class EI>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_potrf_rl(const Seg* __restrict__ segs, int nseg,
                                                   int64_t total, const EI* __restrict__ inA,
                                                   cx<T>* __restrict__ W,
@@ -470,7 +470,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
                 sT[i * 17 + cc] = e;
         }
         wave_lds_sync();
-        fail |= potrf_diag_tile<T, RE>(sT, sD, Lg, Dg, m, 0);
+        fail |= potrf_diag_tile<T>(sT, sD, Lg, Dg, m, 0);
     }
     __syncthreads();
     for (int I = 0; I < S; ++I) {
@@ -486,7 +486,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
                 sa[q] = cur_el(I, i, c0 + tc, i < m && tc < kd);
                 db[q] = tc < kd ? sD[cc * 17 + tc] : czero<T>();
             }
-            Acc3<T, 1, 1, RE> acc;
+            Acc3<T, 1, 1> acc;
             acc.zero();
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -509,7 +509,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
                 // look-ahead: S_JJ -= L_JI L_JI^H for J = I + 1 (sP tile 0),
                 // straight into sT, then the diagonal step of panel J
                 const int J = I + 1, cJ = 16 * J;
-                Acc3<T, 1, 1, RE> acc;
+                Acc3<T, 1, 1> acc;
                 acc.zero();
                 const int ta = cc * 16 + kr;
 #pragma unroll
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
                         sT[i * 17 + cc] = cx<T>{o.r - acc.re(0, 0, v), o.i - acc.im(0, 0, v)};
                 }
                 wave_lds_sync();
-                fail |= potrf_diag_tile<T, RE>(sT, sD, Lg, Dg, m, J);
+                fail |= potrf_diag_tile<T>(sT, sD, Lg, Dg, m, J);
             } else {
                 // the other trailing tiles S_RC -= L_RI L_CI^H, I < C <= R, row
                 // by row (tile 0 is the look-ahead's), TB at a time: their
@@ -562,7 +562,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
                             break;
                         int R, C;
                         tile_rc(e, R, C);
-                        Acc3<T, 1, 1, RE> acc;
+                        Acc3<T, 1, 1> acc;
                         acc.zero();
                         const int ta = (R - I - 1) * 256 + cc * 16 + kr, tb = (C - I - 1) * 256 + cc * 16 + kr;
 #pragma unroll
@@ -590,15 +590,243 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
         atomicMin(&flags[s.sys], fail_key(s.level, s.ob0 + s.obs * p));
 }
 
+// Element of an exchanged tile in LDS: real data keeps the real part only.
+template <class T, bool RE>
+struct lds_el {
+    using type = cx<T>;
+    static __device__ __forceinline__ type to(const cx<T> v) { return v; }
+    static __device__ __forceinline__ cx<T> from(const type v) { return v; }
+};
+template <class T>
+struct lds_el<T, true> {
+    using type = T;
+    static __device__ __forceinline__ type to(const cx<T> v) { return v.r; }
+    static __device__ __forceinline__ cx<T> from(const type v) { return cx<T>{v, T(0)}; }
+};
+
+// ------------------------------------------------------------- k_potrf_reg
+
+// Tiled Cholesky with the whole block in the registers of one work-group, for
+// every tiled block but FP64 complex ones above 128 (whose 544 KB at m = 256
+// exceed a CU's 512 KB of registers).  The accumulators hold the upper tiles
+// V_KI = A_IK^H, K <= I <= S - 1 < SM, of which wave w of SM / 2 owns the tile
+// columns w and S - 1 - w: S + 1 tiles, the same for every wave.  Right-looking
+// over J: U_JI = D_J V_JI (= L_IJ^H) for I > J, then V_KI -= U_JK^H U_JI.  In
+// this form both operands of every product lie in the lanes as accumulators
+// do (see the note in k_elim_mf), so the tiles U_JK pass from their owners to
+// the other waves through LDS in lane order, and only D_J is transposed.  The
+// owner of column J + 1 finishes its diagonal tile first and factors it
+// (tile_chol) while the others update: two barriers per J, no read of L.
+//
+// One block's chain of diagonal steps bounds it: 5.6 us each at m = 256 and
+// also at m = 64, where the kernel from memory took 14 and 6.7 (m = 256: 234
+// -> 91 us per launch of few blocks, 1806 -> 794 us for 2048 real blocks;
+// m = 64 FP64 complex: 27 -> 22 us and 481 -> 297 us for 2048 blocks).
+// The products are summed from zero and subtracted once per J, as k_potrf_rl
+// does: real data gives the same bits in both.
+template <class T, int SM, class EI = cx<T>, bool RE = false>
+__global__ __launch_bounds__(32 * SM) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_potrf_reg(
+    const Seg* __restrict__ segs, int nseg, int64_t total, const EI* __restrict__ inA,
+    cx<T>* __restrict__ W, unsigned long long* __restrict__ flags)
+{
+    using v4 = typename MF<T>::v4;
+    using EL = lds_el<T, RE>;
+    __shared__ typename EL::type sU[SM * 256]; // U_JK: register v of lane l at (4 K + v) 64 + l
+    __shared__ typename EL::type sD[16 * 17];  // D_J
+    __shared__ cx<T> sT[sizeof(T) == 4 ? 16 * 17 : 1];
+    const int tid = threadIdx.x, lane = tid & 63, kr = lane >> 4, cc = lane & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t w = blockIdx.x;
+    if (w >= total)
+        return;
+    const Seg& s = segs[find_seg(segs, nseg, w)];
+    const int64_t t = w - s.w0;
+    const int p = s.e0 + (int)t * s.es;
+    const int m = s.m, S = (m + 15) >> 4;
+    if ((flags[s.sys] >> 40) < (unsigned long long)s.level)
+        return;
+    const int64_t mm = (int64_t)m * m;
+    const EI* Ap = inA + s.oA + (int64_t)p * mm;
+    cx<T>* Lg = W + s.oL + t * mm;
+    cx<T>* Dg = W + s.oD + t * (int64_t)S * 256;
+    // the wave's columns (-1: none); tile (K, b) in slot K, tile (K, a) in slot
+    // SM - K, which never meet
+    const int b = wv <= S - 1 - wv ? S - 1 - wv : -1, a = wv < S - 1 - wv ? wv : -1;
+    v4 vr[SM + 1], vi[RE ? 1 : SM + 1];
+    auto load = [&](v4& xr, v4& xi, int K, int I) {
+        const int i = 16 * I + cc;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int j = 16 * K + MF<T>::row(kr, v);
+            const bool ok = i < m && j <= i; // the lower triangle of A only
+            const cx<T> x = cvt<T>(Ap[ok ? i * m + j : 0]);
+            xr[v] = ok ? x.r : i == j ? T(1) : T(0);
+            if constexpr (!RE)
+                xi[v] = ok ? -x.i : T(0);
+        }
+    };
+#pragma unroll
+    for (int K = 0; K <= SM; ++K) {
+        vr[K] = v4{0, 0, 0, 0};
+        if constexpr (!RE)
+            vi[K] = v4{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int K = 0; K < SM; ++K) {
+        if (K <= b)
+            load(vr[K], vi[RE ? 0 : K], K, b);
+        if (K < SM / 2 && K <= a)
+            load(vr[SM - K], vi[RE ? 0 : SM - K], K, a);
+    }
+    bool fail = false;
+    // diagonal step of column J (the owner's wave) on its finished tile
+    auto diag = [&](int J, const v4 xr, const v4 xi) {
+        cx<double> e[4], l[4], x[4];
+        if constexpr (sizeof(T) == 4) { // rows 4 kr + v: through LDS
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                sT[cc * 17 + MF<T>::row(kr, v)] = cx<T>{xr[v], RE ? T(0) : -xi[v]};
+            wave_lds_sync();
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[v] = cvt<double>(sT[cc * 17 + kr + 4 * v]);
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[v] = cx<double>{xr[v], RE ? 0.0 : -xi[v]};
+        }
+        fail |= tile_chol<T, RE>(x, l, e, m - 16 * J);
+        const int gi = 16 * J + cc;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int u = kr + 4 * v;
+            const cx<T> d = cvt<T>(e[v]);
+            sD[u * 17 + cc] = EL::to(d);
+            Dg[J * 256 + u * 16 + cc] = d;
+            if (gi < m && u <= cc)
+                Lg[gi * m + 16 * J + u] = cvt<T>(l[v]);
+        }
+    };
+    if (wv == 0)
+        diag(0, vr[SM], vi[RE ? 0 : SM]);
+    for (int J = 0;; ++J) {
+        __syncthreads(); // D_J is there, U of J - 1 is read
+        if (J + 1 == S)
+            break;
+        // U_JI of the wave's columns, to LDS and to L
+        if (b > J) {
+            cx<T> d[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                d[v] = EL::from(sD[cc * 17 + MF<T>::row(kr, v)]);
+            auto solve = [&](int I, const v4 xr, const v4 xi) {
+                v4 ur = {0, 0, 0, 0}, ui = {0, 0, 0, 0};
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    ur = MF<T>::mma(d[v].r, xr[v], ur);
+                    if constexpr (!RE) {
+                        ui = MF<T>::mma(d[v].r, xi[v], ui);
+                        ur = MF<T>::mma(d[v].i, -xi[v], ur);
+                        ui = MF<T>::mma(d[v].i, xr[v], ui);
+                    }
+                }
+                const int gi = 16 * I + cc;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    sU[(4 * I + v) * 64 + lane] = EL::to(cx<T>{ur[v], ui[v]});
+                    if (gi < m)
+                        Lg[gi * m + 16 * J + MF<T>::row(kr, v)] = cx<T>{ur[v], RE ? T(0) : -ui[v]};
+                }
+            };
+#pragma unroll
+            for (int K = 0; K < SM; ++K)
+                if (K == J) {
+                    solve(b, vr[K], vi[RE ? 0 : K]);
+                    if (K < SM / 2 && a > J)
+                        solve(a, vr[SM - K], vi[RE ? 0 : SM - K]);
+                }
+        }
+        __syncthreads();
+        if (b <= J)
+            continue;
+        auto operand = [&](int K, cx<T>(&x)[4]) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[v] = EL::from(sU[(4 * K + v) * 64 + lane]);
+        };
+        // the product is summed from zero and subtracted once
+        auto update = [&](v4& xr, v4& xi, const cx<T>(&l)[4], const cx<T>(&r)[4]) {
+            v4 pr = {0, 0, 0, 0}, pi = {0, 0, 0, 0};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                pr = MF<T>::mma(l[v].r, r[v].r, pr);
+                if constexpr (!RE) {
+                    pi = MF<T>::mma(l[v].r, r[v].i, pi);
+                    pr = MF<T>::mma(l[v].i, r[v].i, pr);
+                    pi = MF<T>::mma(l[v].i, -r[v].r, pi);
+                }
+            }
+            // subtracted here: hipcc 7.2 has moved this past the next branch,
+            // where it no longer waits for the matrix unit
+            xr -= pr;
+            asm volatile("" : "+v"(xr));
+            if constexpr (!RE) {
+                xi -= pi;
+                asm volatile("" : "+v"(xi));
+            }
+        };
+        const int J1 = J + 1;
+        if (b == J1 || a == J1) {
+            cx<T> u[4];
+            operand(J1, u);
+            v4 xr = {0, 0, 0, 0}, xi = {0, 0, 0, 0};
+#pragma unroll
+            for (int K = 1; K < SM; ++K)
+                if (K == J1) {
+                    if (K < SM / 2 && a == J1) {
+                        xr = vr[SM - K];
+                        if constexpr (!RE)
+                            xi = vi[SM - K];
+                    } else {
+                        xr = vr[K];
+                        if constexpr (!RE)
+                            xi = vi[K];
+                    }
+                }
+            update(xr, xi, u, u);
+            diag(J1, xr, xi);
+        }
+        if (b > J1) {
+            cx<T> ub[4], ua[4], x[4], xn[4];
+            operand(b, ub);
+            operand(a > 0 ? a : 0, ua);
+            operand(J1, xn);
+#pragma unroll
+            for (int K = 1; K < SM; ++K) {
+                if (K > J && K <= b) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        x[v] = xn[v];
+                    operand(K + 1 < SM ? K + 1 : K, xn);
+                    update(vr[K], vi[RE ? 0 : K], x, ub);
+                    if (K < SM / 2 && K <= a && a > J1)
+                        update(vr[SM - K], vi[RE ? 0 : SM - K], x, ua);
+                }
+            }
+        }
+    }
+    if (lane == 0 && fail)
+        atomicMin(&flags[s.sys], fail_key(s.level, s.ob0 + s.obs * p));
+}
+
 // -------------------------------------------------------------- k_trsm_reg
 
 // Forward substitutions L \ [B_p^H | B_{p-d} | y_p] of the tiled blocks: a
 // work-group of four waves per (block, four 16-column strips), one strip per
-// wave with all its row tiles W_I (at most SM) in accumulator registers from
-// the first load of the right-hand side to the store of the result.
-// Right-looking over the columns J of L: X_J = D_J W_J (the accumulator is the
-// right operand, see the note in k_elim_mf), then W_I -= L_IJ X_J for every
-// I > J -- independent accumulators, so the matrix unit never waits for its
+// wave with all its row tiles of W = L X (at most SM) in accumulator registers.
+// Right-looking over the columns J of L: X_J = D_J (G_J - W_J) (the result is
+// the right operand as it lies, see the note in k_elim_mf), then
+// W_I += L_IJ X_J for every I > J -- independent accumulators, so the matrix unit never waits for its
 // own result.  Column J of L and D_J, the left operands of all four strips,
 // come through LDS once per work-group, column J + 1 being fetched (into
 // registers, then the other LDS buffer) while J is used: one barrier per
@@ -608,23 +836,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
 // FP64 MFMA is what bounds it: 16 (four-multiplication form; real data 4)
 // instructions of 64 cycles per 16 x 16 product against four LDS reads and a
 // quarter of a tile from L2.  Against one wave per strip (or two) that reads
-// its finished rows back from memory, N = 4096, m = 256 real: 13.2 -> 5.7 ms
-// per solve; FP64 complex m = 64 with k = 64, factor and adjoint: 2.54 -> 2.05
+// its finished rows back from memory, N = 4096, m = 256 real: 13.2 -> 4.9 ms
+// per solve; FP64 complex m = 64 with k = 64, factor and adjoint: 2.54 -> 1.97
 // ms.  Eight waves per group halve the passes over L above 128 and were
 // slower all the same (6.8 ms): one barrier then holds up eight strips.
-template <class T, bool RE>
-struct trsm_el { // operand element in LDS: real data keeps the real part only
-    using type = cx<T>;
-    static __device__ __forceinline__ type to(const cx<T> v) { return v; }
-    static __device__ __forceinline__ cx<T> from(const type v) { return v; }
-};
-template <class T>
-struct trsm_el<T, true> {
-    using type = T;
-    static __device__ __forceinline__ type to(const cx<T> v) { return v.r; }
-    static __device__ __forceinline__ cx<T> from(const type v) { return cx<T>{v, T(0)}; }
-};
-
 // Waves per SIMD that the accumulators of SM row tiles (and the column in
 // flight) leave room for.
 template <class T, bool RE, int SM>
@@ -641,7 +856,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trsm_waves<
     const unsigned long long* __restrict__ flags)
 {
     using v4 = typename MF<T>::v4;
-    using EL = trsm_el<T, RE>;
+    using EL = lds_el<T, RE>;
     constexpr int TS = 16 * 17; // a tile in LDS
     __shared__ typename EL::type sC[2][SM * TS]; // D_J, then L_IJ of I > J
     const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, kr = lane >> 4, cc = lane & 15;
@@ -708,23 +923,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trsm_waves<
         if (!RE)
             wi[I] = v4{0, 0, 0, 0};
     }
-    if (nc > 0) { // uniform within the wave
-        const EI* Gc = G + (c0 + min(cc, nc - 1)) * gc;
-        const bool okc = cc < nc;
+    // rows of the right-hand side for column J, fetched a column ahead
+    const EI* Gc = G + (c0 + min(cc, max(nc, 1) - 1)) * gc;
+    const bool okc = cc < nc;
+    EI gn[4] = {};
+    auto rows = [&](int J) {
+        if (nc > 0) { // uniform within the wave; without a strip there is no G
 #pragma unroll
-        for (int I = 0; I < SM; ++I)
-            if (16 * I < m) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int r = 16 * I + MF<T>::row(kr, v);
-                    const cx<T> x = cvt<T>(Gc[min(r, m - 1) * gr]);
-                    const bool ok = okc && r < m;
-                    wr[I][v] = ok ? x.r : T(0);
-                    if constexpr (!RE)
-                        wi[I][v] = ok ? (src == 0 ? -x.i : x.i) : T(0);
-                }
-            }
-    }
+            for (int v = 0; v < 4; ++v)
+                gn[v] = Gc[min(16 * J + MF<T>::row(kr, v), m - 1) * gr];
+        }
+    };
+    rows(0);
     put(0);
     __syncthreads();
     // the columns by recursion: the compiler leaves a loop of this size rolled,
@@ -734,10 +944,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trsm_waves<
         if (J >= S)
             return;
         const typename EL::type* col = sC[J & 1] + cc * 17;
-        if (J + 1 < S)
+        // w = G_J - W_J
+        v4 gr4, gi4 = {0, 0, 0, 0};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const cx<T> x = cvt<T>(gn[v]);
+            const bool ok = okc && 16 * J + MF<T>::row(kr, v) < m;
+            gr4[v] = ok ? x.r - wr[J][v] : T(0);
+            if constexpr (!RE)
+                gi4[v] = ok ? (src == 0 ? -x.i : x.i) - wi[J][v] : T(0);
+        }
+        if (J + 1 < S) {
             fetch(J + 1);
+            rows(J + 1);
+        }
         cx<T> a[4], an[4];
-        v4 xr = {0, 0, 0, 0}, xi = {0, 0, 0, 0}, nr, ni;
+        v4 xr = {0, 0, 0, 0}, xi = {0, 0, 0, 0}, ni;
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             an[v] = czero<T>();
@@ -750,15 +972,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trsm_waves<
             operand(0, a);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                xr = MF<T>::mma(a[v].r, wr[J][v], xr);
+                xr = MF<T>::mma(a[v].r, gr4[v], xr);
                 if constexpr (!RE) {
-                    xi = MF<T>::mma(a[v].r, wi[J][v], xi);
-                    xr = MF<T>::mma(a[v].i, -wi[J][v], xr);
-                    xi = MF<T>::mma(a[v].i, wr[J][v], xi);
+                    xi = MF<T>::mma(a[v].r, gi4[v], xi);
+                    xr = MF<T>::mma(a[v].i, -gi4[v], xr);
+                    xi = MF<T>::mma(a[v].i, gr4[v], xi);
                 }
             }
         }
-        nr = -xr;
         ni = -xi;
         if (J + 1 < SM && nc > 0) {
             operand(1, an);
@@ -773,11 +994,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trsm_waves<
                     operand(I + 1 - J, an);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    wr[I] = MF<T>::mma(a[v].r, nr[v], wr[I]);
+                    wr[I] = MF<T>::mma(a[v].r, xr[v], wr[I]);
                     if constexpr (!RE) {
-                        wi[I] = MF<T>::mma(a[v].r, ni[v], wi[I]);
-                        wr[I] = MF<T>::mma(a[v].i, xi[v], wr[I]);
-                        wi[I] = MF<T>::mma(a[v].i, nr[v], wi[I]);
+                        wi[I] = MF<T>::mma(a[v].r, xi[v], wi[I]);
+                        wr[I] = MF<T>::mma(a[v].i, ni[v], wr[I]);
+                        wi[I] = MF<T>::mma(a[v].i, xr[v], wi[I]);
                     }
                 }
             }
@@ -803,7 +1024,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trsm_waves<
 // its strip without barriers: X_I = D_I (G_I - L_I X) with the finished rows of
 // X read back as the right operand.  Serves FP64 complex blocks above 128, for
 // which the accumulators of k_trsm_reg (256 registers of 512, and scratch)
-// leave one wave per SIMD: N = 1023, m = 200, 2.42 ms per solve here, 2.80
+// leave one wave per SIMD: N = 1023, m = 200, 2.52 ms per solve here, 2.80
 // there.  GD contraction steps per load group: eight for launches of few blocks.
 template <class T, class EI, int GD>
 __global__ __launch_bounds__(64) void k_trsm_strip(const Seg* __restrict__ segs, int nseg,
@@ -870,30 +1091,24 @@ __global__ __launch_bounds__(64) void k_trsm_strip(const Seg* __restrict__ segs,
     const cx<T>* Dg = W + s.oD + t * (int64_t)S * 256;
     for (int I = 0; I < S; ++I) {
         const int r0 = 16 * I;
-        // the accumulator starts at -G_I and ends at -w, w = G_I - L_I X: the
-        // order of k_trsm_reg, so that real data gives the same bits as there.
-        // Register v of lane (kr, cc) holds row MF::row(kr, v) of column cc
         Acc3<T, 1, 1, false> acc;
         acc.zero();
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int r = r0 + MF<T>::row(kr, v);
-            cx<T> g = (r < m && cc < nc) ? cvt<T>(G[r * gr + (c0 + cc) * gc]) : czero<T>();
-            if (src == 0)
-                g.i = -g.i;
-            acc.t1[0][0][v] = -g.r;
-            acc.t3[0][0][v] = -(g.r + g.i);
-        }
         wave_mm3<T, 1, 1, false, false, GD, false>(acc, WOp<T>{Lg + (int64_t)r0 * m, m, 1, m - r0},
                                                    WOp<T>{out + c0, 1, ldo, nc}, r0);
-        // register v is the right operand of contraction step v once the left
-        // operand D_I supplies column MF::row(kr, v) of its row cc
+        // w = G_I - acc stays in the accumulator layout: register v of lane
+        // (kr, cc) holds row MF::row(kr, v) of column cc, which is the right
+        // operand of contraction step v once the left operand D_I supplies
+        // column MF::row(kr, v) of its row cc
         Acc3<T, 1, 1, false> x;
         x.zero();
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const cx<T> a = Dg[I * 256 + cc * 16 + MF<T>::row(kr, v)];
-            x.step(0, 0, a.r, a.i, -acc.re(0, 0, v), -acc.im(0, 0, v));
+            const int rr = MF<T>::row(kr, v), r = r0 + rr;
+            const cx<T> a = Dg[I * 256 + cc * 16 + rr];
+            cx<T> g = (r < m && cc < nc) ? cvt<T>(G[r * gr + (c0 + cc) * gc]) : czero<T>();
+            if (src == 0)
+                g.i = -g.i;
+            x.step(0, 0, a.r, a.i, g.r - acc.re(0, 0, v), g.i - acc.im(0, 0, v));
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
