@@ -1285,6 +1285,12 @@ __global__ __launch_bounds__(64) void k_reduce_big(const Seg* __restrict__ segs,
 // buffers, one barrier per panel).  Items per kept block: the
 // NT (NT + 1) / 2 lower tiles of A', then the NT^2 tiles of B' (NT =
 // ceil(m / 64)).  The right-hand-side tiles y' run in k_reduce_big.
+//
+// FP64 MFMA bounds it (complex 67 % busy).  Real data keeps real parts only in
+// LDS, whose bank conflicts held it at 45 %, and leaves out the 16 x 16 tiles
+// without output: N = 4096, m = 256 real 8.85 -> 7.37 ms per solve.  The loop
+// of a wave with all four tiles is kept free of branches: tests inside it cost
+// complex data 3.87 -> 4.25 ms at N = 1023, m = 200.
 template <class T, class EI = cx<T>, bool RE = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_reduce_lds(const Seg* __restrict__ segs, int nseg,
                                                     int64_t total, int ntile,
@@ -1292,11 +1298,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
                                                     cx<T>* __restrict__ W,
                                                     const unsigned long long* __restrict__ flags)
 {
-    constexpr int KP = 16, LD = 65;
-    __shared__ cx<T> sA[2][KP * LD], sB[2][KP * LD];
+    using EL = lds_el<T, RE>;
+    // real panels: rows 32 banks apart, so that the two rows that half a wave
+    // reads at a time do not meet
+    constexpr int KP = 16, LD = RE ? (sizeof(T) == 8 ? 80 : 72) : 65;
+    __shared__ typename EL::type sA[2][KP * LD], sB[2][KP * LD];
     const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, kr = lane >> 4, cc = lane & 15;
-    const int wa = wv >> 1, wb = wv & 1;
     const int64_t li = xcd_item();
+    // the quarter of each wave turns with the item: the lighter quarters at the
+    // edges of a block fall on every SIMD
+    const int wq = __builtin_amdgcn_readfirstlane((wv + (int)li + (int)(li >> 5)) & 3);
+    const int wa = wq >> 1, wb = wq & 1;
     const int64_t w = li / ntile;
     int u = (int)(li - w * ntile);
     if (w >= total)
@@ -1336,8 +1348,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
     // are P_r^H Q_r
     const int npr = kind == 0 ? (hasL ? 1 : 0) + (hasR ? 1 : 0) : 1;
     const int nkp = (m + KP - 1) / KP, npan = npr * nkp;
-    // quarters above the diagonal of a diagonal tile hold no output
-    const bool live = !(kind == 0 && ti == tj && wb > wa);
+    // 16 x 16 tiles past the block's edge or above the diagonal of A' hold no
+    // output
+    const int ib = i0 + 32 * wa, jb = j0 + 32 * wb;
+    auto on = [&](int a, int b) {
+        return ib + 16 * a < m && jb + 16 * b < m && !(kind == 0 && jb + 16 * b > ib + 16 * a);
+    };
+    const bool on00 = on(0, 0), on01 = on(0, 1), on10 = on(1, 0), on11 = on(1, 1);
+    const bool live = on00 || on01 || on10 || on11, full = on00 && on01 && on10 && on11;
     // thread tid moves elements e = tid + 256 e4 of a 16 x 64 panel: row
     // e / 64, column e % 64
     cx<T> ra0, ra1, ra2, ra3, rb0, rb1, rb2, rb3;
@@ -1363,14 +1381,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
 #define CRS_PANEL_STORE(b)                                                                         \
     do {                                                                                           \
         const int o_ = (tid >> 6) * LD + (tid & 63);                                                \
-        sA[b][o_] = ra0;                                                                            \
-        sA[b][o_ + 4 * LD] = ra1;                                                                   \
-        sA[b][o_ + 8 * LD] = ra2;                                                                   \
-        sA[b][o_ + 12 * LD] = ra3;                                                                  \
-        sB[b][o_] = rb0;                                                                            \
-        sB[b][o_ + 4 * LD] = rb1;                                                                   \
-        sB[b][o_ + 8 * LD] = rb2;                                                                   \
-        sB[b][o_ + 12 * LD] = rb3;                                                                  \
+        sA[b][o_] = EL::to(ra0);                                                                            \
+        sA[b][o_ + 4 * LD] = EL::to(ra1);                                                                   \
+        sA[b][o_ + 8 * LD] = EL::to(ra2);                                                                   \
+        sA[b][o_ + 12 * LD] = EL::to(ra3);                                                                  \
+        sB[b][o_] = EL::to(rb0);                                                                            \
+        sB[b][o_ + 4 * LD] = EL::to(rb1);                                                                   \
+        sB[b][o_ + 8 * LD] = EL::to(rb2);                                                                   \
+        sB[b][o_ + 12 * LD] = EL::to(rb3);                                                                  \
     } while (0)
     Acc3<T, 2, 2, RE> acc;
     acc.zero();
@@ -1383,32 +1401,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
         const int b = pn & 1;
         if (pn + 1 < npan)
             CRS_PANEL_LOAD(pn + 1);
-        if (live) {
+        auto operands = [&](int ks, cx<T>(&x)[2], cx<T>(&y)[2]) {
+            const int row = 4 * ks + kr;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                x[i] = EL::from(sA[b][row * LD + 32 * wa + 16 * i + cc]);
+                y[i] = EL::from(sB[b][row * LD + 32 * wb + 16 * i + cc]);
+                x[i].i = -x[i].i; // conj: the left operand is X^H
+            }
+        };
+        if (full) {
 #pragma unroll
             for (int ks = 0; ks < KP / 4; ++ks) {
-                const int row = 4 * ks + kr;
-                T ar[2], ai[2], as[2], br[2], bi[2], bs[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const cx<T> x = sA[b][row * LD + 32 * wa + 16 * i + cc];
-                    ar[i] = x.r;
-                    ai[i] = -x.i; // conj: the left operand is X^H
-                    as[i] = ar[i] + ai[i];
-                    const cx<T> y = sB[b][row * LD + 32 * wb + 16 * i + cc];
-                    br[i] = y.r;
-                    bi[i] = y.i;
-                    bs[i] = br[i] + bi[i];
-                }
+                cx<T> x[2], y[2];
+                operands(ks, x, y);
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        acc.t1[i][j] = MF<T>::mma(ar[i], br[j], acc.t1[i][j]);
-                        if constexpr (!RE) {
-                            acc.t2[i][j] = MF<T>::mma(ai[i], bi[j], acc.t2[i][j]);
-                            acc.t3[i][j] = MF<T>::mma(as[i], bs[j], acc.t3[i][j]);
-                        }
-                    }
+                    for (int j = 0; j < 2; ++j)
+                        acc.step(i, j, x[i].r, x[i].i, y[j].r, y[j].i);
+            }
+        } else if (live) {
+#pragma unroll
+            for (int ks = 0; ks < KP / 4; ++ks) {
+                cx<T> x[2], y[2];
+                operands(ks, x, y);
+                if (on00)
+                    acc.step(0, 0, x[0].r, x[0].i, y[0].r, y[0].i);
+                if (on01)
+                    acc.step(0, 1, x[0].r, x[0].i, y[1].r, y[1].i);
+                if (on10)
+                    acc.step(1, 0, x[1].r, x[1].i, y[0].r, y[0].i);
+                if (on11)
+                    acc.step(1, 1, x[1].r, x[1].i, y[1].r, y[1].i);
             }
         }
         if (pn + 1 < npan)
@@ -1417,7 +1442,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
     }
 #undef CRS_PANEL_LOAD
 #undef CRS_PANEL_STORE
-    const int ib = i0 + 32 * wa, jb = j0 + 32 * wb;
     if (kind == 0) {
         const EI* Aq = inA + s.oA + q * mm;
         cx<T>* Vo = W + s.oAo + oi * mm;
