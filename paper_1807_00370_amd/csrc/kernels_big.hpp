@@ -1483,7 +1483,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
 //   phase A, all waves at once: w_J = g_J - Q_J x_{p-d} - P_J x_{p+d}, kept
 //     in the MFMA accumulators;
 //   phase B, bottom-up over the tiles I: wave I forms x_I = D_I^H w_I (the
-//     accumulator is the right operand, see k_trsm_big), stores it and
+//     accumulator is the right operand, see k_trsm_reg), stores it and
 //     publishes it in LDS; every wave J < I then applies
 //     w_J -= L_IJ^H x_I (its operand loaded one step ahead).
 // The block's serial chain is S short steps instead of S full tile sweeps.
