@@ -1288,9 +1288,10 @@ __global__ __launch_bounds__(64) void k_reduce_big(const Seg* __restrict__ segs,
 //
 // FP64 MFMA bounds it (complex 67 % busy).  Real data keeps real parts only in
 // LDS, whose bank conflicts held it at 45 %, and leaves out the 16 x 16 tiles
-// without output: N = 4096, m = 256 real 8.85 -> 7.37 ms per solve.  The loop
-// of a wave with all four tiles is kept free of branches: tests inside it cost
-// complex data 3.87 -> 4.25 ms at N = 1023, m = 200.
+// without output: N = 4096, m = 256 real 8.85 -> 7.37 ms per solve.  Complex data
+// runs all four tiles of a quarter: leaving some out cost the loop its
+// schedule (N = 4096, m = 256: 18.3 -> 20.2 ms with y'; with tests inside the
+// loop N = 1023, m = 200 3.87 -> 4.25 ms).
 template <class T, class EI = cx<T>, bool RE = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_reduce_lds(const Seg* __restrict__ segs, int nseg,
                                                     int64_t total, int ntile,
@@ -1305,9 +1306,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
     __shared__ typename EL::type sA[2][KP * LD], sB[2][KP * LD];
     const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, kr = lane >> 4, cc = lane & 15;
     const int64_t li = xcd_item();
-    // the quarter of each wave turns with the item: the lighter quarters at the
-    // edges of a block fall on every SIMD
-    const int wq = __builtin_amdgcn_readfirstlane((wv + (int)li + (int)(li >> 5)) & 3);
+    // real data: the quarter of each wave turns with the item, so that the
+    // lighter quarters at the edges of a block fall on every SIMD
+    const int wq = RE ? __builtin_amdgcn_readfirstlane((wv + (int)li + (int)(li >> 5)) & 3) : wv;
     const int wa = wq >> 1, wb = wq & 1;
     const int64_t w = li / ntile;
     int u = (int)(li - w * ntile);
@@ -1349,13 +1350,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
     const int npr = kind == 0 ? (hasL ? 1 : 0) + (hasR ? 1 : 0) : 1;
     const int nkp = (m + KP - 1) / KP, npan = npr * nkp;
     // 16 x 16 tiles past the block's edge or above the diagonal of A' hold no
-    // output
+    // output (complex data: quarters above the diagonal only)
     const int ib = i0 + 32 * wa, jb = j0 + 32 * wb;
     auto on = [&](int a, int b) {
         return ib + 16 * a < m && jb + 16 * b < m && !(kind == 0 && jb + 16 * b > ib + 16 * a);
     };
     const bool on00 = on(0, 0), on01 = on(0, 1), on10 = on(1, 0), on11 = on(1, 1);
-    const bool live = on00 || on01 || on10 || on11, full = on00 && on01 && on10 && on11;
+    const bool live = on00 || on01 || on10 || on11;
+    const bool full = RE ? on00 && on01 && on10 && on11 : !(kind == 0 && ti == tj && wb > wa);
     // thread tid moves elements e = tid + 256 e4 of a 16 x 64 panel: row
     // e / 64, column e % 64
     cx<T> ra0, ra1, ra2, ra3, rb0, rb1, rb2, rb3;
@@ -1421,7 +1423,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) voi
                     for (int j = 0; j < 2; ++j)
                         acc.step(i, j, x[i].r, x[i].i, y[j].r, y[j].i);
             }
-        } else if (live) {
+        } else if (RE && live) {
 #pragma unroll
             for (int ks = 0; ks < KP / 4; ++ks) {
                 cx<T> x[2], y[2];
