@@ -315,10 +315,14 @@ __device__ __forceinline__ void tile_nn3(Acc3<T, 1, 1>& acc, const cx<T>* __rest
 //     row broadcasts;
 //   - beside it lane group k eliminates column k of the panel's identity,
 //     which leaves M = [D_pp; -L_below D_pp], one entry per lane;
-//   - one 4-term product on MFMA updates the whole trailing tile,
-//     S -= L_p L_p^H (the lane's own entry of L_p is both operands), and one
-//     more all of D, D_{p..} = M D_p (the lane's own accumulator is the right
-//     operand).
+//   - one 4-term product on MFMA adds the panel's products to the sums of the
+//     whole tile, W += L_p L_p^H (the lane's own entry of L_p is both
+//     operands), and one more forms all of D, D_{p..} = M D_p (the lane's own
+//     accumulator is the right operand).
+// Every entry's products are summed from zero and subtracted from it once, when
+// its column is factored: sums that start from the entry round every product
+// at the diagonal's size, and the error of a solve was 5 to 8 % larger (m = 16:
+// 6.67e-16 against 6.98e-16, m = 32: 7.55e-16 against 8.09e-16).
 // A panel's chain is four pivots long; the 16 x 16 updates leave it.  The
 // chain of dependent FP64 operations bounds it.  Measured, FP64 complex, one
 // wave: 5560 cycles for L and D; a column at a time on the vector unit, every
@@ -360,6 +364,18 @@ __device__ __forceinline__ void gather_groups(double x, double (&o)[4])
         o[g] = __longlong_as_double((long long)(((unsigned long long)q[1][g] << 32) | q[0][g]));
 }
 
+template <bool RE>
+__device__ __forceinline__ void gather_groups(const cx<double> x, cx<double> (&o)[4])
+{
+    double r[4], i[4] = {0, 0, 0, 0};
+    gather_groups(x.r, r);
+    if constexpr (!RE)
+        gather_groups(x.i, i);
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        o[g] = cx<double>{r[g], i[g]};
+}
+
 // Column C = 4 P + J of the panel's identity: row C is scaled by the inverse
 // pivot, the rows below subtract their L_rC times it.
 template <int C, bool RE>
@@ -379,29 +395,31 @@ __device__ __forceinline__ void tile_inv_col(cx<double>& q, const cx<double> l, 
 }
 
 template <class T, bool RE, int P, int J>
-__device__ __forceinline__ void tile_chol_col(cx<double> (&c)[4], cx<double>& q, int r,
-                                              int mr, unsigned long long& fail)
+__device__ __forceinline__ void tile_chol_col(const cx<double> (&s)[4], cx<double> (&c)[4], cx<double>& q,
+                                              int r, int mr, unsigned long long& fail)
 {
     constexpr int C = 4 * P + J;
-    const double d = row_bcast<C>(c[J].r);
+    const cx<double> x{(sizeof(T) == 8 ? s[J].r : 0.0) - c[J].r,
+                       RE ? 0.0 : (sizeof(T) == 8 ? s[J].i : 0.0) - c[J].i};
+    const double d = row_bcast<C>(x.r);
     const double inv = round_to<T>(rsqrt_nr(d));
     fail |= C < mr ? __ballot(!(d > 0.0)) : 0ull;
     asm volatile("" : "+s"(fail)); // compared now, not with all 16 pivots kept
-    const cx<double> l{round_to<T>(c[J].r * inv), RE ? 0.0 : round_to<T>(c[J].i * inv)};
-    auto sub = [&](cx<double>& x, double ur, double ui) { // x -= l conj(u)
-        x.r = fma(-l.r, ur, x.r);
+    const cx<double> l{round_to<T>(x.r * inv), RE ? 0.0 : round_to<T>(x.i * inv)};
+    auto add = [&](cx<double>& w, double ur, double ui) { // w += l conj(u)
+        w.r = fma(l.r, ur, w.r);
         if constexpr (!RE) {
-            x.r = fma(-l.i, ui, x.r);
-            x.i = fma(-l.i, ur, x.i);
-            x.i = fma(l.r, ui, x.i);
+            w.r = fma(l.i, ui, w.r);
+            w.i = fma(l.i, ur, w.i);
+            w.i = fma(-l.r, ui, w.i);
         }
     };
     if constexpr (J < 1)
-        sub(c[1], row_bcast<4 * P + 1>(l.r), RE ? 0.0 : row_bcast<4 * P + 1>(l.i));
+        add(c[1], row_bcast<4 * P + 1>(l.r), RE ? 0.0 : row_bcast<4 * P + 1>(l.i));
     if constexpr (J < 2)
-        sub(c[2], row_bcast<4 * P + 2>(l.r), RE ? 0.0 : row_bcast<4 * P + 2>(l.i));
+        add(c[2], row_bcast<4 * P + 2>(l.r), RE ? 0.0 : row_bcast<4 * P + 2>(l.i));
     if constexpr (J < 3)
-        sub(c[3], row_bcast<4 * P + 3>(l.r), RE ? 0.0 : row_bcast<4 * P + 3>(l.i));
+        add(c[3], row_bcast<4 * P + 3>(l.r), RE ? 0.0 : row_bcast<4 * P + 3>(l.i));
     tile_inv_col<C, RE>(q, l, inv, r);
     c[J] = l;
 }
@@ -421,34 +439,38 @@ __device__ __forceinline__ void tile_inv_panel(d4v& er, d4v& ei, const cx<double
     }
 }
 
-template <class T, bool RE, int P>
-__device__ __forceinline__ void tile_chol_panel(d4v& sr, d4v& si, d4v& er, d4v& ei, cx<double> (&L)[4],
-                                                int r, int g, int mr,
+// The panel's entries s and the sums c of the products to subtract from them
+// (T = float: c holds both, in double).
+template <class T, bool RE, bool HW, int P>
+__device__ __forceinline__ void tile_chol_panel(const cx<double> s, d4v& wr, d4v& wi, d4v& er, d4v& ei,
+                                                cx<double> (&L)[4], int r, int g, int mr,
                                                 unsigned long long& fail)
 {
-    cx<double> c[4], q{r == 4 * P + g ? 1.0 : 0.0, 0.0};
-    double xr[4], xi[4] = {0, 0, 0, 0};
-    gather_groups(sr[P], xr);
-    if constexpr (!RE)
-        gather_groups(si[P], xi);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        c[j] = cx<double>{xr[j], xi[j]};
-    tile_chol_col<T, RE, P, 0>(c, q, r, mr, fail);
-    tile_chol_col<T, RE, P, 1>(c, q, r, mr, fail);
-    tile_chol_col<T, RE, P, 2>(c, q, r, mr, fail);
-    tile_chol_col<T, RE, P, 3>(c, q, r, mr, fail);
+    cx<double> a[4], c[4], q{r == 4 * P + g ? 1.0 : 0.0, 0.0};
+    if constexpr (sizeof(T) == 4)
+        gather_groups<RE>(cx<double>{wr[P] - s.r, wi[P] - s.i}, c);
+    else {
+        gather_groups<RE>(s, a);
+        if constexpr (HW || P > 0)
+            gather_groups<RE>(cx<double>{wr[P], wi[P]}, c);
+        else
+            c[0] = c[1] = c[2] = c[3] = czero<double>();
+    }
+    tile_chol_col<T, RE, P, 0>(a, c, q, r, mr, fail);
+    tile_chol_col<T, RE, P, 1>(a, c, q, r, mr, fail);
+    tile_chol_col<T, RE, P, 2>(a, c, q, r, mr, fail);
+    tile_chol_col<T, RE, P, 3>(a, c, q, r, mr, fail);
     const bool b0 = g & 1, b1 = g & 2;
     cx<double> l;
     l.r = b1 ? (b0 ? c[3].r : c[2].r) : (b0 ? c[1].r : c[0].r);
     l.i = RE ? 0.0 : (b1 ? (b0 ? c[3].i : c[2].i) : (b0 ? c[1].i : c[0].i));
     L[P] = l;
     if constexpr (P < 3) {
-        sr = MF<double>::mma(-l.r, l.r, sr);
+        wr = MF<double>::mma(l.r, l.r, wr);
         if constexpr (!RE) {
-            si = MF<double>::mma(-l.r, l.i, si);
-            sr = MF<double>::mma(-l.i, l.i, sr);
-            si = MF<double>::mma(l.i, l.r, si);
+            wi = MF<double>::mma(l.r, l.i, wi);
+            wr = MF<double>::mma(l.i, l.i, wr);
+            wi = MF<double>::mma(-l.i, l.r, wi);
         }
     }
     tile_inv_panel<RE, P>(er, ei, q);
@@ -464,26 +486,22 @@ __device__ __forceinline__ void tile_identity(d4v& er, d4v& ei, int r, int g)
 }
 
 // s: the lane's entries (cc, kr + 4 v) of the tile (those right of the
-// diagonal may hold anything) -> L: the same entries of the factor, the
-// diagonal as {L_rr, 1 / L_rr}; e: entries (kr + 4 v, cc) of D.  Returns true
-// if one of the first mr pivots is not > 0 (the same in every lane).
-template <class T, bool RE = false>
-__device__ __forceinline__ bool tile_chol(const cx<double> (&s)[4], cx<double> (&L)[4],
+// diagonal may hold anything), wr + i wi: of the products to subtract from it
+// (HW: not all zero) -> L: the same entries of the factor, the diagonal as {L_rr, 1 / L_rr}; e:
+// entries (kr + 4 v, cc) of D.  Returns true if one of the first mr pivots is
+// not > 0 (the same in every lane).
+template <class T, bool RE = false, bool HW = true>
+__device__ __forceinline__ bool tile_chol(const cx<double> (&s)[4], d4v wr, d4v wi, cx<double> (&L)[4],
                                           cx<double> (&e)[4], int mr)
 {
     const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-    d4v sr, si, er, ei;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        sr[v] = s[v].r;
-        si[v] = s[v].i;
-    }
+    d4v er, ei;
     tile_identity(er, ei, r, g);
     unsigned long long fail = 0;
-    tile_chol_panel<T, RE, 0>(sr, si, er, ei, L, r, g, mr, fail);
-    tile_chol_panel<T, RE, 1>(sr, si, er, ei, L, r, g, mr, fail);
-    tile_chol_panel<T, RE, 2>(sr, si, er, ei, L, r, g, mr, fail);
-    tile_chol_panel<T, RE, 3>(sr, si, er, ei, L, r, g, mr, fail);
+    tile_chol_panel<T, RE, HW, 0>(s[0], wr, wi, er, ei, L, r, g, mr, fail);
+    tile_chol_panel<T, RE, HW, 1>(s[1], wr, wi, er, ei, L, r, g, mr, fail);
+    tile_chol_panel<T, RE, HW, 2>(s[2], wr, wi, er, ei, L, r, g, mr, fail);
+    tile_chol_panel<T, RE, HW, 3>(s[3], wr, wi, er, ei, L, r, g, mr, fail);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         e[v] = cx<double>{er[v], ei[v]};
@@ -491,6 +509,12 @@ __device__ __forceinline__ bool tile_chol(const cx<double> (&s)[4], cx<double> (
             L[v].i = er[v];
     }
     return fail != 0;
+}
+template <class T, bool RE = false>
+__device__ __forceinline__ bool tile_chol(const cx<double> (&s)[4], cx<double> (&L)[4],
+                                          cx<double> (&e)[4], int mr)
+{
+    return tile_chol<T, RE, false>(s, d4v{0, 0, 0, 0}, d4v{0, 0, 0, 0}, L, e, mr);
 }
 
 // Storage of a factor of 8 < m <= 32 (in LDS and in the workspace): the packed
@@ -693,28 +717,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void
                     row1[MF<T>::row(kr, v)] = aL[v];
             }
             wave_lds_sync();
-            // S_11 = A_11 - L_10 L_10^H in the layout of tile_chol: the lane's
-            // entries of L_10 are both operands
+            // L_10 L_10^H, to be subtracted from A_11, in the layout of
+            // tile_chol: the lane's entries of L_10 are both operands
             tile_load<T>(sL, 1, m, t);
-            d4v pr, pi;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                pr[v] = t[v].r;
-                pi[v] = t[v].i;
-            }
+            d4v pr = {0, 0, 0, 0}, pi = {0, 0, 0, 0};
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const cx<double> x = sizeof(T) == 8 ? cvt<double>(aL[v])
                                                     : (i1 < m ? cvt<double>(row1[kr + 4 * v]) : czero<double>());
-                pr = MF<double>::mma(-x.r, x.r, pr);
-                pi = MF<double>::mma(-x.r, x.i, pi);
-                pr = MF<double>::mma(-x.i, x.i, pr);
-                pi = MF<double>::mma(x.i, x.r, pi);
+                pr = MF<double>::mma(x.r, x.r, pr);
+                pi = MF<double>::mma(x.r, x.i, pi);
+                pr = MF<double>::mma(x.i, x.i, pr);
+                pi = MF<double>::mma(-x.i, x.r, pi);
             }
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                t[v] = cx<double>{pr[v], pi[v]};
-            fail |= tile_chol<T>(t, L, e, m - 16);
+            fail |= tile_chol<T>(t, pr, pi, L, e, m - 16);
             tile_store<T>(sL, 1, m, e);
             wave_lds_sync();
             tile_operand<T, false>(sL, 1, m, aD[1]);
