@@ -498,10 +498,18 @@ __device__ __forceinline__ bool tile_chol(const cx<double> (&s)[4], d4v wr, d4v 
     d4v er, ei;
     tile_identity(er, ei, r, g);
     unsigned long long fail = 0;
+    L[1] = L[2] = L[3] = czero<double>();
+    mr = __builtin_amdgcn_readfirstlane(mr);
+    // panels past the block's edge hold identity rows, which D has already
     tile_chol_panel<T, RE, HW, 0>(s[0], wr, wi, er, ei, L, r, g, mr, fail);
-    tile_chol_panel<T, RE, HW, 1>(s[1], wr, wi, er, ei, L, r, g, mr, fail);
-    tile_chol_panel<T, RE, HW, 2>(s[2], wr, wi, er, ei, L, r, g, mr, fail);
-    tile_chol_panel<T, RE, HW, 3>(s[3], wr, wi, er, ei, L, r, g, mr, fail);
+    if (mr > 4) {
+        tile_chol_panel<T, RE, HW, 1>(s[1], wr, wi, er, ei, L, r, g, mr, fail);
+        if (mr > 8) {
+            tile_chol_panel<T, RE, HW, 2>(s[2], wr, wi, er, ei, L, r, g, mr, fail);
+            if (mr > 12)
+                tile_chol_panel<T, RE, HW, 3>(s[3], wr, wi, er, ei, L, r, g, mr, fail);
+        }
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         e[v] = cx<double>{er[v], ei[v]};
