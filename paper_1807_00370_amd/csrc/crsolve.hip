@@ -192,7 +192,7 @@ struct crsolve_plan {
     // launch shapes of the levels with few blocks (autotuner): waves per
     // level for the split elimination, block count below which the reduced
     // system is formed one wave per 16 x 16 tile
-    int64_t tail_waves = 2048, tail_blocks = 1024;
+    int64_t tail_waves = 1024, tail_blocks = 1024;
 
     // recorded HIP graphs (crsolve_set_graphs)
     struct GraphEntry {
@@ -438,9 +438,17 @@ unsigned grid8(int64_t items) { return (unsigned)((items + 7) / 8 * 8); }
 // by one block's chain of dependent steps, not by throughput.  There the
 // elimination splits each block's strips over up to tail_waves / blocks
 // waves, and launches of at most tail_blocks blocks form the reduced system
-// one wave per 16 x 16 output tile.  Defaults 2048 and 1024 (measured on the
-// N = 65536, m = 32 workload; 2048 is about the wave slots of the GPU's 1024
-// SIMDs); the autotuner picks both per plan.
+// one wave per 16 x 16 output tile.  Defaults 1024 and 1024; the autotuner
+// picks both per plan.
+//
+// 1024 is one wave per SIMD: every wave of a block factors it, and two that
+// share a SIMD take turns.  Against 2048, Algorithm 1 in FP64 complex, us:
+// N = 300, m = 32, k = 2 365 -> 310, N = 1000, m = 17 539 -> 507, m = 9 214 ->
+// 189, one-sided N = 4000, m = 32 542 -> 532; right-hand sides alone the same
+// within 1 %.  Blocks of two tiles with 513 to 704 in a launch are the
+// exception, two waves each though SIMDs are shared (N = 600 and 700, m = 17,
+// k = 40: 529 -> 483 and 565 -> 514; N = 800 and one tile lose 5 to 10 % by
+// it).
 
 bool mf_class(int cls) { return cls == 2 || cls == 3; }
 
@@ -512,7 +520,10 @@ void run_elim(const Ctx& c, const Launch& L, const void* A, const void* B, const
     if (mf_class(L.cls)) {
         const BigDims b = big_dims(c.p, L);
         const int nst = (mat ? 2 * b.S : 0) + (rhs ? b.K16 : 0);
-        nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(nst, c.p->tail_waves / L.total));
+        int64_t per = std::max<int64_t>(1, c.p->tail_waves / L.total);
+        if (per == 1 && kClsM[L.cls] > 16 && 16 * L.total <= 11 * c.p->tail_waves)
+            per = 2;
+        nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(nst, per));
     }
 #define CALL(MT) Disp<T, EI, RE>::template elim<MT>(L, c.dsegs, inA, inB, iny, c.ws, c.flags, mat, rhs, c.st, v, nsplit)
     CRS_BY_CLASS(L.cls, CALL)

@@ -46,3 +46,19 @@ def test_bad_pivot_in_partial_tile(cuda_ok, m):
     rec = sol.info_host()
     assert (rec["status"] == np.r_[np.ones(m), 0]).all()
     assert (rec["level"][:m] == 0).all() and (rec["block"][:m] == 1).all()
+
+
+@pytest.mark.parametrize("N,m,k", [(600, 20, 40), (300, 9, 17), (513, 32, 1), (705, 17, 33)])
+def test_same_bits_for_any_split(cuda_ok, N, m, k):
+    """How many waves share a block does not change a bit of x."""
+    import torch
+    from paper_1807_00370_amd.solver import Solver
+    dev = torch.device("cuda:0")
+    s = W.random_hpd(N, m, k, 9800 + m)
+    A, B, y = (torch.from_numpy(v).to(dev) for v in (s.A, s.B, s.y))
+    sol = Solver([N], [m], [k], device=dev, schedule="pcr")
+    x = sol.factor_solve(A, B, y).clone()
+    assert sol.info_host()[0]["status"] == 0
+    for waves in (1, 1024, 4 * N, 1 << 20):
+        sol.plan.set_tuning("tw=%d;" % waves)
+        assert torch.equal(sol.factor_solve(A, B, y), x)
