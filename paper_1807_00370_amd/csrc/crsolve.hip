@@ -273,6 +273,21 @@ struct Timed {
 struct Shape {
     unsigned grid, nthr;
 };
+// Launches of the kernels of m <= 8 with fewer waves than this (two per SIMD)
+// deal the right-hand-side columns of a block over several waves: one wave
+// walking through all of them is what bounds such a level.  small_split is the
+// log2 of the waves per block, for at most `chunks` passes of one wave.
+// us, one wave per block / the work-group kernels / with the rule: N = 32,
+// m = 8, k = 64, stored factors 115 / 93 / 76; N = 1000, m = 4, k = 1024 2114 /
+// 1917 / 260; N = 32, m = 2, k = 1024 785 / 593 / 99 with the factorization.
+constexpr int64_t kSmallWaves = 2048;
+int small_split(int64_t waves, int chunks)
+{
+    int ss = 0;
+    while ((1 << ss) < chunks && (waves << ss) < kSmallWaves)
+        ++ss;
+    return ss;
+}
 Shape small_shape(int64_t waves)
 {
     const int per = waves >= 2048 ? 4 : 1;
@@ -290,7 +305,7 @@ struct Disp {
     template <int MT>
     static void elim(const Launch& L, const Seg* segs, const void* inA, const void* inB,
                      const void* iny, void* W, unsigned long long* flags, int mat, int rhs,
-                     hipStream_t st, int variant, int nsplit)
+                     hipStream_t st, int variant, int nsplit, int kmax)
     {
         if constexpr (MT == 16 || MT == 32) {
             hipLaunchKernelGGL((crs::k_elim_mf<T, MT, EI>),
@@ -299,10 +314,18 @@ struct Disp {
                                (const EI*)inB, (const EI*)iny, (cx<T>*)W, flags, mat, rhs);
         } else if constexpr (MT > 32) { // blocks above 32 run the tiled kernels
         } else if (variant == 0) {
-            const Shape g = small_shape((L.total * 4 * MT + 63) / 64);
-            hipLaunchKernelGGL((crs::k_elim_s<T, MT, EI>), dim3(g.grid), dim3(g.nthr), 0, st,
-                               segs + L.seg0, L.nseg, L.total, (const EI*)inA,
-                               (const EI*)inB, (const EI*)iny, (cx<T>*)W, flags, mat, rhs);
+            const int64_t waves = (L.total * 4 * MT + 63) / 64;
+            const int ss = small_split(waves, (kmax - (mat ? MT : 0) + 4 * MT - 1) / (4 * MT));
+            const Shape g = small_shape(waves << ss);
+            auto go = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(g.grid), dim3(g.nthr), 0, st, segs + L.seg0, L.nseg,
+                                   L.total, ss, (const EI*)inA, (const EI*)inB, (const EI*)iny,
+                                   (cx<T>*)W, flags, rhs);
+            };
+            if (mat)
+                go(crs::k_elim_s<T, MT, true, EI>);
+            else
+                go(crs::k_elim_s<T, MT, false, EI>);
         } else {
             constexpr int PW = sizeof(T) == 8 ? 32 : 64;
             hipLaunchKernelGGL((crs::k_elim<T, MT, kNT, PW, EI>), dim3(grid_of(L.total)), dim3(kNT), 0,
@@ -313,16 +336,18 @@ struct Disp {
     template <int MT>
     static void reduce(const Launch& L, const Seg* segs, const void* inA, const void* iny, void* W,
                        const unsigned long long* flags, int mat, int rhs, hipStream_t st,
-                       int variant)
+                       int variant, int kmax)
     {
         if ((MT == 16 || MT == 32) && variant == 0) {
             hipLaunchKernelGGL((crs::k_reduce_m<T, (MT == 16 || MT == 32) ? MT : 16, EI>), dim3((unsigned)L.total), dim3(64), 0, st,
                                segs + L.seg0, L.nseg, L.total, (const EI*)inA,
                                (const EI*)iny, (cx<T>*)W, flags, mat, rhs);
         } else if (MT <= 8 && variant == 0) {
-            const Shape g = small_shape((L.total * MT + 7) / 8);
+            const int64_t waves = (L.total * MT + 7) / 8;
+            const int ss = small_split(waves, 1 + (kmax - MT + 2 * MT - 1) / (2 * MT));
+            const Shape g = small_shape(waves << ss);
             hipLaunchKernelGGL((crs::k_reduce_s<T, MT <= 8 ? MT : 8, EI>), dim3(g.grid), dim3(g.nthr), 0, st,
-                               segs + L.seg0, L.nseg, L.total, (const EI*)inA,
+                               segs + L.seg0, L.nseg, L.total, ss, (const EI*)inA,
                                (const EI*)iny, (cx<T>*)W, flags, mat, rhs);
         } else if (MT == 64) {
             hipLaunchKernelGGL((crs::k_reduce_t<T, 64, EI>), dim3((unsigned)L.total), dim3(64), 0, st,
@@ -346,9 +371,9 @@ struct Disp {
         } else if constexpr (MT > 32) { // blocks above 32 run the tiled kernels
         } else if (variant == 0) {
             // right-hand-side columns side by side, as many as a wave has
-            // lanes for one block
+            // lanes for one block, and beyond a wave while waves are few
             int cs = 0;
-            while ((1 << cs) < kmax && (MT << cs) < 64)
+            while ((1 << cs) < kmax && ((MT << cs) < 64 || (L.total * MT << cs) < 64 * kSmallWaves))
                 ++cs;
             const Shape g = small_shape((((L.total * MT) << cs) + 63) / 64);
             hipLaunchKernelGGL((crs::k_back_s<T, MT>), dim3(g.grid), dim3(g.nthr), 0, st, segs + L.seg0,
@@ -425,6 +450,15 @@ BigDims big_dims(const crsolve_plan* p, const Launch& L)
 // of loads in flight in launches of fewer blocks than this, which are bound by
 // one strip's chain, and four in others (at 64 blocks 345 -> 325 us).
 constexpr int64_t kTrsmStripBlocks = 256;
+
+// Largest number of right-hand-side columns of a launch.
+int kmax_of(const crsolve_plan* p, const Launch& L)
+{
+    int k = 1;
+    for (int i = L.seg0; i < L.seg0 + L.nseg; ++i)
+        k = std::max(k, p->segs[i].k);
+    return k;
+}
 
 // FP64 complex Cholesky above 128: launches of at most this many blocks (one
 // per CU) run k_potrf_rl, 144 us per launch of few blocks at m = 200; 512 blocks
@@ -525,7 +559,7 @@ void run_elim(const Ctx& c, const Launch& L, const void* A, const void* B, const
             per = 2;
         nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(nst, per));
     }
-#define CALL(MT) Disp<T, EI, RE>::template elim<MT>(L, c.dsegs, inA, inB, iny, c.ws, c.flags, mat, rhs, c.st, v, nsplit)
+#define CALL(MT) Disp<T, EI, RE>::template elim<MT>(L, c.dsegs, inA, inB, iny, c.ws, c.flags, mat, rhs, c.st, v, nsplit, rhs ? kmax_of(c.p, L) : 0)
     CRS_BY_CLASS(L.cls, CALL)
 #undef CALL
 }
@@ -584,7 +618,7 @@ void run_reduce(const Ctx& c, const Launch& L, const void* A, const void* y, int
                                (const EI*)iny, (cx<T>*)c.ws, c.flags);
         return;
     }
-#define CALL(MT) Disp<T, EI, RE>::template reduce<MT>(L, c.dsegs, inA, iny, c.ws, c.flags, mat, rhs, c.st, v)
+#define CALL(MT) Disp<T, EI, RE>::template reduce<MT>(L, c.dsegs, inA, iny, c.ws, c.flags, mat, rhs, c.st, v, rhs ? kmax_of(c.p, L) : 0)
     CRS_BY_CLASS(L.cls, CALL)
 #undef CALL
 }
@@ -605,9 +639,7 @@ void run_back(const Ctx& c, const Launch& L, void* x, int upd)
         return;
     }
     const int v = c.p->var[2][L.cls][L.f64];
-    int kmax = 1;
-    for (int i = L.seg0; i < L.seg0 + L.nseg; ++i)
-        kmax = std::max(kmax, c.p->segs[i].k);
+    const int kmax = kmax_of(c.p, L);
 #define CALL(MT) Disp<T>::template back<MT>(L, c.dsegs, c.ws, X, c.flags, c.st, v, x, u, kmax)
     CRS_BY_CLASS(L.cls, CALL)
 #undef CALL

@@ -11,6 +11,10 @@
 //   k_back_s    one row of an eliminated block per lane, 64 / MT blocks (or
 //               right-hand-side columns of a block) per wave.
 //
+// Launches of few waves deal a block's columns of y over 2^ss waves (2^cs lane
+// groups in k_back_s); in the elimination with the matrix each of them factors
+// the block and wave 0 alone stores the factor, P, Q and the first columns.
+//
 // Rows and columns from m to MT are padded with the identity (A) or zero.
 //
 // All three are bound by HBM at levels with many blocks and by the latency of
@@ -60,24 +64,33 @@ __device__ __forceinline__ double group_bcast(double x)
 
 // ----------------------------------------------------------------- k_elim_s
 
-// Step C of the elimination on one column x (rows C..MT-1), with column C of
-// L in l (diagonal {L_CC, 1 / L_CC}).
+// The elimination from step C on of one column x (rows C..MT-1), with column C
+// of L in l (diagonal {L_CC, 1 / L_CC}); the next column of L is read a step
+// ahead, and no earlier (registers).
 template <class T, int MT, int C>
-__device__ __forceinline__ void col_step(cx<T> (&x)[MT], const cx<T>* l)
+__device__ __forceinline__ void col_solve(cx<T> (&x)[MT], const cx<T>* sL, const cx<T> (&l)[MT])
 {
+    cx<T> ln[MT];
+#pragma unroll
+    for (int r = 0; r < MT; ++r)
+        ln[r] = C + 1 < MT && r > C ? sL[(C + 1) * MT + r] : czero<T>();
     const T inv = l[C].i;
     x[C] = cx<T>{x[C].r * inv, x[C].i * inv};
 #pragma unroll
     for (int r = C + 1; r < MT; ++r)
         msub(x[r], l[r], x[C]);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (C + 1 < MT)
+        col_solve<T, MT, C + 1>(x, sL, ln);
 }
-template <class T, int MT, int C>
+template <class T, int MT>
 __device__ __forceinline__ void col_solve(cx<T> (&x)[MT], const cx<T>* sL)
 {
-    if constexpr (C < MT) {
-        col_step<T, MT, C>(x, sL + C * MT);
-        col_solve<T, MT, C + 1>(x, sL);
-    }
+    cx<T> l[MT];
+#pragma unroll
+    for (int r = 0; r < MT; ++r)
+        l[r] = sL[r];
+    col_solve<T, MT, 0>(x, sL, l);
 }
 
 // Column C of the factorization: lane j = C of the A part owns it (rows
@@ -118,20 +131,26 @@ __device__ __forceinline__ void factor_steps(cx<T> (&x)[MT], cx<T>* sL, T& iv, b
     }
 }
 
-template <class T, int MT, class EI = cx<T>>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_elim_s(const Seg* __restrict__ segs, int nseg, int64_t total,
+// MAT: with the matrix (and the first MT columns of y_p); else the columns of
+// y_p against the stored factor.  That form is an instance of its own: it
+// needs 191 registers for FP64, MT = 8, where both in one kernel spilled at any
+// bound that the matrix pass runs well with (N = 131071, m = 8, k = 1, stored
+// factors 740 -> 458 us).
+template <class T, int MT, bool MAT, class EI = cx<T>>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAT ? 3 : 2, 8))) void k_elim_s(const Seg* __restrict__ segs, int nseg, int64_t total, int ss,
                                                 const EI* __restrict__ inA, const EI* __restrict__ inB,
                                                 const EI* __restrict__ iny, cx<T>* __restrict__ W,
-                                                unsigned long long* __restrict__ flags, int with_mat,
-                                                int with_rhs)
+                                                unsigned long long* __restrict__ flags, int with_rhs)
 {
     constexpr int LB = 4 * MT, NB = 64 / LB; // lanes per block, blocks per wave
     constexpr int LT = MT + 1;
     // a block's A_p and B_p for the transposition, then its factor
-    __shared__ cx<T> sAll[4][NB][2 * MT * LT];
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __shared__ cx<T> sAll[4][NB][MAT ? 2 * MT * LT : MT * MT];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int blk = lane / LB, cl = lane % LB, part = cl / MT, j = cl % MT;
-    const int64_t w = ((int64_t)blockIdx.x * (blockDim.x >> 6) + wv) * NB + blk;
+    const int64_t wi = (int64_t)blockIdx.x * (blockDim.x >> 6) + wv;
+    const int nsplit = 1 << ss, sp = (int)wi & (nsplit - 1); // waves per block, this one
+    const int64_t w = (wi >> ss) * NB + blk;
     bool live = w < total;
     const Seg& s = segs[find_seg(segs, nseg, live ? w : 0)];
     const int64_t t = live ? w - s.w0 : 0;
@@ -139,14 +158,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
     const int m = s.m, k = s.k, d = s.d;
     const int mm = m * m, mk = m * k;
     const bool hasPrev = p - d >= 0, hasNext = p + d < s.n;
-    // a system that broke down at an earlier level stops here
+    // a system that broke down at an earlier level stores nothing (the loads
+    // do not wait for its flag)
+    const bool in = live;
     live = live && (flags[s.sys] >> 40) >= (unsigned long long)s.level;
     cx<T>* Lg = W + s.oL + t * mm;
     cx<T>* sL = sAll[wv][blk];
     const EI* yp = iny + s.oy + (int64_t)p * mk;
     cx<T>* gp = W + s.og + t * mk;
-    int c0 = 0;
-    if (with_mat) {
+    // the columns of y_p beyond those that a matrix pass takes along, one per
+    // lane of the block
+    const int c0 = (MAT ? MT : 0) + sp * LB + cl, kc = with_rhs ? k : 0;
+    cx<T> yc[MT];
+    auto load_col = [&](int c) {
+#pragma unroll
+        for (int r = 0; r < MT; ++r) {
+            const bool ok = c < kc && r < m;
+            const cx<T> v = cvt<T>(yp[ok ? r * k + c : 0]);
+            yc[r] = pick(ok, v, czero<T>());
+        }
+    };
+    if constexpr (MAT) {
         // element r of the lane's column: A_p's (from the lower triangle),
         // B_p^H's, B_{p-d}'s or y_p's.  Every lane loads down its column of
         // the stored block, so that a load covers MT consecutive elements of
@@ -155,8 +187,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
         const EI* Ap = inA + s.oA + (int64_t)p * mm;
         const EI* src = part == 0 ? Ap
                                   : part == 3 ? yp : inB + s.oB + (int64_t)(part == 1 ? p : p - d) * mm;
-        const bool on = live && j < (part == 3 ? k : m) &&
-                        (part == 0 || (part == 1 ? hasNext : part == 2 ? hasPrev : with_rhs != 0));
+        const bool on = in && j < (part == 3 ? k : m) &&
+                        (part == 0 || (sp == 0 && (part == 1 ? hasNext : part == 2 ? hasPrev : with_rhs != 0)));
         const int ld = part == 3 ? k : m;
         EI in[MT];
 #pragma unroll
@@ -187,9 +219,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
         T iv = T(1);
         bool fail = false;
         factor_steps<T, MT, 0>(x, sL, iv, part == 0, j, m, fail);
-        if (fail && live)
+        if (fail && live && sp == 0)
             atomicMin(&flags[s.sys], fail_key(s.level, s.ob0 + s.obs * p));
-        if (on) {
+        if (on && live && sp == 0) {
             if (part == 0) {
                 // packed lower triangle, the inverse pivot in the imaginary
                 // slot of the diagonal
@@ -205,32 +237,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
                         out[r * ld + j] = x[r];
             }
         }
-        c0 = MT;
     } else {
+        // the packed factor, dealt over the block's lanes, into columns (lanes
+        // past the end move the last element); what the padded rows and
+        // columns hold reaches no stored row
+        constexpr int NE = (MT * (MT + 1) / 2 + LB - 1) / LB;
+        const int np = m * (m + 1) / 2;
+        cx<T> l[NE];
 #pragma unroll
-        for (int r = 0; r < MT; ++r) {
-            const bool ok = live && part == 0 && j <= r && r < m;
-            const cx<T> v = ld_or0(Lg + r * (r + 1) / 2 + j, Lg, ok);
-            if (part == 0)
-                sL[j * MT + r] = r == j && !ok ? cx<T>{T(1), T(1)} : v;
+        for (int q = 0; q < NE; ++q)
+            l[q] = Lg[min(cl + LB * q, np - 1)];
+        load_col(c0); // beside L
+#pragma unroll
+        for (int q = 0; q < NE; ++q) {
+            const int e = min(cl + LB * q, np - 1), r = tri_row(e);
+            sL[(e - r * (r + 1) / 2) * MT + r] = l[q];
         }
         wave_lds_sync();
     }
-    // the other columns of y_p, one per lane of the block
-    if (with_rhs && live)
-        for (int c = c0 + cl; c < k; c += LB) {
-            cx<T> x[MT];
+    for (int c = c0; live && c < kc; c += LB * nsplit) {
+        if (MAT || c > c0)
+            load_col(c);
+        col_solve<T, MT>(yc, sL);
 #pragma unroll
-            for (int r = 0; r < MT; ++r) {
-                const cx<T> v = cvt<T>(yp[r < m ? r * k + c : c]);
-                x[r] = pick(r < m, v, czero<T>());
-            }
-            col_solve<T, MT, 0>(x, sL);
-#pragma unroll
-            for (int r = 0; r < MT; ++r)
-                if (r < m)
-                    gp[r * k + c] = x[r];
-        }
+        for (int r = 0; r < MT; ++r)
+            if (r < m)
+                gp[r * k + c] = yc[r];
+    }
 }
 
 // --------------------------------------------------------------- k_reduce_s
@@ -243,7 +276,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 // complex form.
 template <class T, int MT, class EI = cx<T>>
 __global__ __launch_bounds__(256) void k_reduce_s(const Seg* __restrict__ segs, int nseg,
-                                                  int64_t total, const EI* __restrict__ inA,
+                                                  int64_t total, int ss, const EI* __restrict__ inA,
                                                   const EI* __restrict__ iny, cx<T>* __restrict__ W,
                                                   const unsigned long long* __restrict__ flags,
                                                   int with_mat, int with_rhs)
@@ -252,8 +285,9 @@ __global__ __launch_bounds__(256) void k_reduce_s(const Seg* __restrict__ segs, 
     constexpr int NB = 8 / MT, KS = MT / 4, CW = 16 / NB;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int kr = lane >> 4, cc = lane & 15;
-    const int64_t w0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + wv) * NB;
-    const int64_t w = w0 + (NB == 1 ? 0 : cc / CW);
+    const int64_t wi = (int64_t)blockIdx.x * (blockDim.x >> 6) + wv;
+    const int nsplit = 1 << ss, sp = (int)wi & (nsplit - 1); // waves per block, this one
+    const int64_t w = (wi >> ss) * NB + (NB == 1 ? 0 : cc / CW);
     bool live = w < total;
     const Seg& s = segs[find_seg(segs, nseg, live ? w : 0)];
     const int64_t t = live ? w - s.w0 : 0;
@@ -262,8 +296,10 @@ __global__ __launch_bounds__(256) void k_reduce_s(const Seg* __restrict__ segs, 
     const int l = q - d, r = q + d;
     const int64_t oi = s.out_by_pos ? q : t;
     const int mm = m * m, mk = m * k;
-    live = live && (flags[s.sys] >> 40) > (unsigned long long)s.level;
+    // (the loads do not wait for the flag)
     const bool hasL = live && l >= 0, hasR = live && r < n, hasF = hasR && r + d < n;
+    const bool in = live;
+    live = live && (flags[s.sys] >> 40) > (unsigned long long)s.level;
     const int64_t tl = hasL ? (l - s.e0) / s.es : 0, tr = hasR ? (r - s.e0) / s.es : 0;
     const cx<T>* Pl = W + s.oP + tl * mm;
     const cx<T>* Qr = W + s.oQ + tr * mm;
@@ -277,7 +313,9 @@ __global__ __launch_bounds__(256) void k_reduce_s(const Seg* __restrict__ segs, 
     cx<T>* yo = W + s.oyo + oi * mk;
     const bool second = (cc / MT) & 1; // P_r / g columns
     const int col = cc % MT;
-    const int kc = with_rhs ? min(k, MT) : 0;
+    const int kc = with_rhs && sp == 0 ? min(k, MT) : 0;
+    if (sp)
+        with_mat = 0;
     // operands: left Q_r | P_r and P_l | 0, right Q_r | g_r and P_l | g_l
     cx<T> xr[KS], yr[KS], xl[KS], yl[KS];
 #pragma unroll
@@ -295,7 +333,7 @@ __global__ __launch_bounds__(256) void k_reduce_s(const Seg* __restrict__ segs, 
         yl[u] = second ? gy : b;
     }
     // what the results are subtracted from: A_q for (Q, Q), y_q for (Q, g)
-    cx<T> in[4];
+    cx<T> base[4];
     bool put[4];
     cx<T>* dst[4];
     bool diag[4];
@@ -303,15 +341,15 @@ __global__ __launch_bounds__(256) void k_reduce_s(const Seg* __restrict__ segs, 
     for (int v = 0; v < 4; ++v) {
         const int i = MF<T>::row(kr, v), a = i % MT;
         const bool same = NB == 1 || i / CW == cc / CW, rowP = (i / MT) & 1;
-        const bool isA = same && !rowP && !second && with_mat && live && a < m && col <= a;
+        const bool isA = same && !rowP && !second && with_mat && in && a < m && col <= a;
         const bool isF = same && rowP && !second && with_mat && hasF && a < m && col < m;
-        const bool isY = same && !rowP && second && live && a < m && col < kc;
+        const bool isY = same && !rowP && second && in && a < m && col < kc;
         const EI* src = isA ? Aq + a * m + col : isY ? yq + a * k + col : yq;
-        in[v] = cvt<T>(*(isA || isY ? src : (with_mat ? inA + s.oA : iny + s.oy)));
+        base[v] = cvt<T>(*(isA || isY ? src : (with_mat ? inA + s.oA : iny + s.oy)));
         if (!(isA || isY))
-            in[v] = czero<T>();
+            base[v] = czero<T>();
         diag[v] = isA && a == col;
-        put[v] = isA || isF || isY;
+        put[v] = live && (isA || isF || isY);
         dst[v] = isA ? Vo + a * m + col : isF ? Fo + a * m + col : yo + a * k + col;
     }
     v4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0};
@@ -330,10 +368,11 @@ __global__ __launch_bounds__(256) void k_reduce_s(const Seg* __restrict__ segs, 
 #pragma unroll
     for (int v = 0; v < 4; ++v)
         if (put[v])
-            *dst[v] = cx<T>{in[v].r - cr[v], diag[v] ? T(0) : in[v].i - ci[v]};
+            *dst[v] = cx<T>{base[v].r - cr[v], diag[v] ? T(0) : base[v].i - ci[v]};
     if (!with_rhs)
         return;
-    for (int c0 = MT; __any(c0 < k); c0 += CW) {
+    // the chunks of columns beyond MT; wave 0 of several has had the matrix
+    for (int c0 = MT + CW * (sp ? sp - 1 : nsplit - 1); __any(c0 < k); c0 += CW * nsplit) {
         const int c = c0 + cc % CW;
         cr = v4{0, 0, 0, 0};
         ci = v4{0, 0, 0, 0};
@@ -348,7 +387,7 @@ __global__ __launch_bounds__(256) void k_reduce_s(const Seg* __restrict__ segs, 
         for (int v = 0; v < 4; ++v) {
             const int i = MF<T>::row(kr, v), a = i % MT;
             put[v] = (NB == 1 || i / CW == cc / CW) && !((i / MT) & 1) && live && a < m && c < k;
-            in[v] = cvt<T>(yq[put[v] ? a * k + c : 0]);
+            base[v] = cvt<T>(yq[put[v] ? a * k + c : 0]);
         }
 #pragma unroll
         for (int u = 0; u < KS; ++u)
@@ -359,7 +398,7 @@ __global__ __launch_bounds__(256) void k_reduce_s(const Seg* __restrict__ segs, 
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             if (put[v])
-                yo[(MF<T>::row(kr, v) % MT) * k + c] = cx<T>{in[v].r - cr[v], in[v].i - ci[v]};
+                yo[(MF<T>::row(kr, v) % MT) * k + c] = cx<T>{base[v].r - cr[v], base[v].i - ci[v]};
     }
 }
 
@@ -432,8 +471,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
                                                 const unsigned long long* __restrict__ flags,
                                                 cx<double>* __restrict__ U, int upd)
 {
-    const int lane = threadIdx.x & 63, r = lane % MT, cg = (lane / MT) & ((1 << cs) - 1);
-    const int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / MT >> cs;
+    const int64_t id = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / MT;
+    const int r = threadIdx.x % MT, cg = (int)(id & ((1 << cs) - 1));
+    const int64_t w = id >> cs;
     if (w >= total)
         return;
     const Seg& s = segs[find_seg(segs, nseg, w)];
