@@ -277,9 +277,9 @@ struct Shape {
 // deal the right-hand-side columns of a block over several waves: one wave
 // walking through all of them is what bounds such a level.  small_split is the
 // log2 of the waves per block, for at most `chunks` passes of one wave.
-// us, one wave per block / the work-group kernels / with the rule: N = 32,
-// m = 8, k = 64, stored factors 115 / 93 / 76; N = 1000, m = 4, k = 1024 2114 /
-// 1917 / 260; N = 32, m = 2, k = 1024 785 / 593 / 99 with the factorization.
+// us, one wave per block / the work-group kernels / with the rule: stored
+// factors N = 32, m = 8, k = 64 115 / 92 / 68; N = 1000, m = 4, k = 1024 2114 /
+// 1911 / 238; with the factorization N = 32, m = 2, k = 1024 785 / 593 / 71.
 constexpr int64_t kSmallWaves = 2048;
 int small_split(int64_t waves, int chunks)
 {
