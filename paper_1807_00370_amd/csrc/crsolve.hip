@@ -465,6 +465,14 @@ int kmax_of(const crsolve_plan* p, const Launch& L)
 // take 342 us with k_potrf_big.
 constexpr int64_t kPotrfWideBlocks = 256;
 
+// FP32 right-hand sides alone with blocks above 64: launches of one strip a
+// block, or of at most this many strips, run k_trsm_few.  Solve against stored
+// factors, us, k_trsm_reg / k_trsm_few: complex m = 200, k = 1, N = 16 and 600
+// 365 / 237 and 1193 / 964; k = 64, N = 600 2006 / 1843; where the first level
+// is beyond the rule k_trsm_reg is ahead there: real N = 3000, m = 144, k = 64
+// 2557 / 2680.
+constexpr int64_t kTrsmFew = 2048;
+
 // Grid of the tiled kernels: a multiple of 8 work-groups (see xcd_item).
 unsigned grid8(int64_t items) { return (unsigned)((items + 7) / 8 * 8); }
 
@@ -527,6 +535,13 @@ void run_elim(const Ctx& c, const Launch& L, const void* A, const void* B, const
                                    c.dsegs + L.seg0, L.nseg, L.total, ngrp, per, mat, rhs,
                                    (const EI*)inB, (const EI*)iny, (cx<T>*)c.ws, c.flags);
             };
+            if constexpr (sizeof(T) == 4)
+                if (!mat && b.S > 4 && (ns == 1 || L.total * ns <= kTrsmFew)) {
+                    hipLaunchKernelGGL((crs::k_trsm_few<T, EI, RE>), dim3(grid8(L.total * ns)), dim3(64 * b.S),
+                                       0, c.st, c.dsegs + L.seg0, L.nseg, L.total, ns, (const EI*)iny,
+                                       (cx<T>*)c.ws, c.flags);
+                    return;
+                }
             if (b.S <= 4)
                 go(crs::k_trsm_reg<T, 4, EI, RE>);
             else if (b.S <= 8)

@@ -1018,6 +1018,115 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trsm_waves<
     column(column, std::integral_constant<int, 0>{});
 }
 
+// -------------------------------------------------------------- k_trsm_few
+
+// The right-hand sides alone in FP32, few strips a block: a strip of k_trsm_reg
+// is one wave's chain of S (S + 1) / 2 tile products, with idle waves beside
+// it.  Here a work-group has one strip and one wave per row tile (blockDim = 64 x
+// the largest tile count of the launch): wave J forms X_J = D_J (G_J - W_J) and
+// passes it on through LDS, the waves I > J add L_IJ X_J to their W_I.  A tile of
+// L has one reader then and comes straight from memory, a column ahead.  The
+// products and their order are those of k_trsm_reg: the same bits.
+template <class T, class EI = cx<T>, bool RE = false>
+__global__ __launch_bounds__(1024) void k_trsm_few(const Seg* __restrict__ segs, int nseg,
+                                                   int64_t total, int nstrip,
+                                                   const EI* __restrict__ iny, cx<T>* __restrict__ W,
+                                                   const unsigned long long* __restrict__ flags)
+{
+    using v4 = typename MF<T>::v4;
+    __shared__ cx<T> sX[2][256]; // X_J: register v of lane l at 64 v + l
+    const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t li = xcd_item();
+    const int64_t w = li / nstrip;
+    const int c0 = 16 * (int)(li - w * nstrip);
+    if (w >= total)
+        return;
+    const Seg& s = segs[find_seg(segs, nseg, w)];
+    const int64_t t = w - s.w0;
+    const int p = s.e0 + (int)t * s.es;
+    const int m = s.m, k = s.k, S = (m + 15) >> 4;
+    if (c0 >= k || (flags[s.sys] >> 40) < (unsigned long long)s.level)
+        return;
+    const int64_t mm = (int64_t)m * m, mk = (int64_t)m * k;
+    const int nc = min(16, k - c0);
+    // the wave's tile; one past the block's edge (a smaller block in a launch
+    // of larger ones) reads no L and stores nothing
+    const int r0 = 16 * wv, row = r0 + cc;
+    const bool own = wv < S;
+    const cx<T>* Lr = W + s.oL + t * mm + (int64_t)min(row, m - 1) * m;
+    const cx<T>* Dg = W + s.oD + t * (int64_t)S * 256 + min(wv, S - 1) * 256 + cc * 16;
+    const EI* G = iny + s.oy + (int64_t)p * mk + c0 + min(cc, nc - 1);
+    cx<T>* out = W + s.og + t * mk + c0 + cc;
+    cx<T> a[4], an[4], d[4], g[4];
+    auto fetch = [&](int J) { // L_IJ, J < I = wv < S: columns below 16 I < m
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const cx<T> x = Lr[16 * J + MF<T>::row(kr, v)];
+            an[v] = cx<T>{row < m ? x.r : T(0), row < m ? x.i : T(0)};
+        }
+    };
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        an[v] = czero<T>();
+    if (own && wv > 0)
+        fetch(0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int rr = MF<T>::row(kr, v);
+        const bool ok = cc < nc && r0 + rr < m;
+        d[v] = Dg[rr];
+        const cx<T> x = cvt<T>(G[(int64_t)min(r0 + rr, m - 1) * k]);
+        g[v] = cx<T>{ok ? x.r : T(0), ok ? x.i : T(0)};
+    }
+    v4 wr = {0, 0, 0, 0}, wi = {0, 0, 0, 0};
+    for (int J = 0; J < S; ++J) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            a[v] = an[v];
+        if (own && wv > J + 1)
+            fetch(J + 1);
+        if (wv == J) {
+            v4 xr = {0, 0, 0, 0}, xi = {0, 0, 0, 0};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const bool ok = cc < nc && r0 + MF<T>::row(kr, v) < m;
+                const T br = ok ? g[v].r - wr[v] : T(0), bi = ok ? g[v].i - wi[v] : T(0);
+                xr = MF<T>::mma(d[v].r, br, xr);
+                if constexpr (!RE) {
+                    xi = MF<T>::mma(d[v].r, bi, xi);
+                    xr = MF<T>::mma(d[v].i, -bi, xr);
+                    xi = MF<T>::mma(d[v].i, br, xi);
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int r = r0 + MF<T>::row(kr, v);
+                const cx<T> x{xr[v], RE ? T(0) : xi[v]};
+                sX[J & 1][64 * v + lane] = x;
+                if (r < m && cc < nc)
+                    out[(int64_t)r * k] = x;
+            }
+        }
+        __syncthreads();
+        if (own && wv > J) {
+            cx<T> x[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[v] = sX[J & 1][64 * v + lane];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                wr = MF<T>::mma(a[v].r, x[v].r, wr);
+                if constexpr (!RE) {
+                    wi = MF<T>::mma(a[v].r, x[v].i, wi);
+                    wr = MF<T>::mma(a[v].i, -x[v].i, wr);
+                    wi = MF<T>::mma(a[v].i, x[v].r, wi);
+                }
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------ k_trsm_strip
 
 // One wave per (eliminated block, 16-column strip), sweeping the row tiles of
