@@ -460,11 +460,6 @@ int kmax_of(const crsolve_plan* p, const Launch& L)
     return k;
 }
 
-// FP64 complex Cholesky above 128: launches of at most this many blocks (one
-// per CU) run k_potrf_rl, 144 us per launch of few blocks at m = 200; 512 blocks
-// take 342 us with k_potrf_big.
-constexpr int64_t kPotrfWideBlocks = 256;
-
 // FP32 right-hand sides alone with blocks above 64: launches of one strip a
 // block, or of at most this many strips, run k_trsm_few.  Solve against stored
 // factors, us, k_trsm_reg / k_trsm_few: complex m = 200, k = 1, N = 16 and 600
@@ -514,15 +509,9 @@ void run_elim(const Ctx& c, const Launch& L, const void* A, const void* B, const
                 go(crs::k_potrf_reg<T, 4, EI, RE>, 128);
             else if (b.S <= 8)
                 go(crs::k_potrf_reg<T, 8, EI, RE>, 256);
-            else if constexpr (sizeof(T) == 8 && !RE) {
-                // FP64 complex above 128 exceeds a CU's registers.  Few blocks:
-                // one block's chain of panels sets the time, so the diagonal
-                // steps run ahead of the trailing updates
-                if (L.total <= kPotrfWideBlocks)
-                    go(crs::k_potrf_rl<T, EI>, 512);
-                else
-                    go(crs::k_potrf_big<T, EI>, 256);
-            } else
+            else if constexpr (sizeof(T) == 8 && !RE) // exceeds a CU's registers
+                go(crs::k_potrf_rl<T, EI>, 512);
+            else
                 go(crs::k_potrf_reg<T, 16, EI, RE>, 512);
         }
         const int ns = (mat ? 2 * b.S : 0) + (rhs ? b.K16 : 0);

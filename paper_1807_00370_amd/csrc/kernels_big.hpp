@@ -8,8 +8,7 @@
 //                 16-column panels.  Each 16 x 16 diagonal tile is factored
 //                 and inverted by one wave (tile_chol); its inverse
 //                 D_I = L_II^{-1} is kept for the substitutions.
-//   k_potrf_big, k_potrf_rl   the same from memory, for FP64 complex blocks
-//                 above 128 (launches of many and of few blocks).
+//   k_potrf_rl    the same from memory, for FP64 complex blocks above 128.
 //   k_trsm_reg    one wave per (eliminated block, 16-column strip of
 //                 [B_p^H | B_{p-d} | y_p]), four strips of a block per
 //                 work-group: blocked forward substitution
@@ -313,102 +312,11 @@ __device__ __forceinline__ bool potrf_diag_tile(cx<T>* sT, cx<T>* sD, cx<T>* __r
     return fail;
 }
 
-// ------------------------------------------------------------- k_potrf_big
-
-template <class T, class EI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_potrf_big(const Seg* __restrict__ segs, int nseg,
-                                                   int64_t total, const EI* __restrict__ inA,
-                                                   cx<T>* __restrict__ W,
-                                                   unsigned long long* __restrict__ flags)
-{
-    using v4 = typename MF<T>::v4;
-    __shared__ cx<T> sT[16 * 17]; // diagonal tile S_I (row-major, leading dimension 17)
-    __shared__ cx<T> sD[16 * 17]; // D_I for the tiles below the diagonal (leading dimension 17)
-    __shared__ int sFail;
-    const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, kr = lane >> 4, cc = lane & 15;
-    const int nw = blockDim.x >> 6;
-    const int64_t w = blockIdx.x;
-    if (w >= total)
-        return;
-    const Seg& s = segs[find_seg(segs, nseg, w)];
-    const int64_t t = w - s.w0;
-    const int p = s.e0 + (int)t * s.es;
-    const int m = s.m, S = (m + 15) >> 4;
-    if ((flags[s.sys] >> 40) < (unsigned long long)s.level)
-        return; // broke down at an earlier level
-    const int64_t mm = (int64_t)m * m;
-    const EI* Ap = inA + s.oA + (int64_t)p * mm;
-    cx<T>* Lg = W + s.oL + t * mm;
-    cx<T>* Dg = W + s.oD + t * (int64_t)S * 256;
-    if (tid == 0)
-        sFail = 0;
-    for (int I = 0; I < S; ++I) {
-        const int c0 = 16 * I;
-        // panel column I: S_R = A[R][I] - L[R][<I] L[I][<I]^H for R >= I (the
-        // Hermitian reading of A: lower triangle of the diagonal tile only)
-        for (int R = I + wv; R < S; R += nw) {
-            Acc3<T, 1, 1> acc;
-            acc.zero();
-            wave_mm3<T, 1, 1, false, true, 4>(acc, WOp<T>{Lg + (int64_t)16 * R * m, m, 1, m - 16 * R},
-                                              WOp<T>{Lg + (int64_t)c0 * m, m, 1, m - c0}, c0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = 16 * R + MF<T>::row(kr, v), j = c0 + cc;
-                if (i < m && j < m && (R > I || j <= i)) {
-                    const cx<T> a = cvt<T>(Ap[(int64_t)i * m + j]);
-                    const cx<T> o{a.r - acc.re(0, 0, v), a.i - acc.im(0, 0, v)};
-                    if (R == I) // the diagonal tile goes to wave 0 through LDS
-                        sT[(i - c0) * 17 + (j - c0)] = o;
-                    else
-                        Lg[(int64_t)i * m + j] = o;
-                }
-            }
-        }
-        __syncthreads();
-        // diagonal tile: L_II and D_I (wave 0)
-        if (wv == 0) {
-            const bool fail = potrf_diag_tile<T>(sT, sD, Lg, Dg, m, I);
-            if (lane == 0 && fail)
-                sFail = 1;
-        }
-        __syncthreads();
-        // tiles below the diagonal: L[R][I] = S_R D_I^H, in place.  Step q of
-        // the contraction: lane (kr, cc) supplies S_R[cc][4 q + kr] and
-        // conj(D_I[cc][4 q + kr]), the latter read from the LDS array itself
-        // (a generic pointer would give flat loads, which wait behind the
-        // wave's global stores of its previous tile)
-        for (int R = I + 1 + wv; R < S; R += nw) {
-            const int kd = min(16, m - c0);
-            cx<T> sa[4], db[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = 16 * R + cc, tc = 4 * q + kr;
-                sa[q] = (i < m && tc < kd) ? Lg[(int64_t)i * m + c0 + tc] : czero<T>();
-                db[q] = tc < kd ? sD[cc * 17 + tc] : czero<T>();
-            }
-            Acc3<T, 1, 1> acc;
-            acc.zero();
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                acc.step(0, 0, sa[q].r, sa[q].i, db[q].r, -db[q].i);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = 16 * R + MF<T>::row(kr, v), j = c0 + cc;
-                if (i < m && j < m)
-                    Lg[(int64_t)i * m + j] = cx<T>{acc.re(0, 0, v), acc.im(0, 0, v)};
-            }
-        }
-        __syncthreads();
-    }
-    if (tid == 0 && sFail)
-        atomicMin(&flags[s.sys], fail_key(s.level, s.ob0 + s.obs * p));
-}
-
 // -------------------------------------------------------------- k_potrf_rl
 
-// Right-looking form of the tiled Cholesky for launches of few blocks
-// (m > 64, one work-group of eight waves per block), where one block's chain
-// of panels sets the time.  Per 16-column panel I: the waves form the tiles
+// Right-looking tiled Cholesky from memory, for the FP64 complex blocks above
+// 128 that do not fit k_potrf_reg: one work-group of eight waves per block, whose
+// chain of panels sets the time.  Per 16-column panel I: the waves form the tiles
 // below the diagonal, L_RI = S_RI D_I^H, into L and into LDS; then wave 0
 // runs ahead on the next panel -- S_JJ -= L_JI L_JI^H for J = I + 1, straight
 // into LDS, and the diagonal step of panel J (potrf_diag_tile: L_JJ, D_J) --
@@ -419,8 +327,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 // the work-group.  Panel 0 reads the tiles of A (Hermitian reading: lower
 // triangle, the diagonal's imaginary parts dropped when a diagonal tile is
 // factored) and writes every lower tile of the slot once; later panels read
-// and update the slot.  The trailing sums round once per panel: the same
-// factorization as k_potrf_big up to rounding order.
+// and update the slot.  Every panel's products are summed from zero and
+// subtracted once, as in k_potrf_reg: real data gives the same bits in both.
+//
+// A left-looking form (one sum over all panels, other bits) was as fast in
+// launches of more than 256 blocks: N = 600, 1023, 4096, m = 200 6705, 9389, 28835
+// us a solve with it, 6689, 9364, 29020 without; m = 256, N = 4096 42.98 and 43.37
+// ms.
 template <class T, class EI>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_potrf_rl(const Seg* __restrict__ segs, int nseg,
                                                   int64_t total, const EI* __restrict__ inA,
