@@ -5,6 +5,7 @@
 * FP64 complex blocks above 128, imaginary parts and partial tiles included, with
   more than 256 of them in a launch: a batch of copies of a few systems, each
   copy the same bits as its system alone, and the oracle's solution.
+* Blocks of 1..4 in FP64 with so many waves that work-groups hold four.
 
 Tolerance as in the parity tests: 1e-11 of the largest entry (kappa <= 10).
 """
@@ -67,3 +68,21 @@ def test_wide_complex_blocks_in_one_launch(cuda_ok, m, k):
         xo, io = oracle.solve_cr(s.A, s.B, s.y)
         assert io["status"] == 0
         assert np.abs(alone.cpu().numpy() - xo).max() <= 1e-11 * np.abs(xo).max()
+
+
+@pytest.mark.parametrize("dtype", ["complex128", "float64"])
+@pytest.mark.parametrize("N,m,k", [(17001, 3, 2), (16400, 4, 1), (20000, 1, 5), (9001, 8, 1)])
+def test_many_small_blocks(cuda_ok, N, m, k, dtype):
+    import torch
+    from paper_1807_00370_amd.solver import Solver
+    print("case many small N=%d m=%d k=%d %s" % (N, m, k, dtype), flush=True)
+    dev, dt = torch.device("cuda:0"), getattr(torch, dtype)
+    s = (W.random_spd if dtype == "float64" else W.random_hpd)(N, m, k, 9450 + m)
+    A, B, y = (torch.from_numpy(v).to(dev).to(dt) for v in (s.A, s.B, s.y))
+    sol = Solver([N], [m], [k], dtype=dt, device=dev)
+    x = sol.factor_solve(A, B, y)
+    sol.factor(A, B)
+    assert torch.equal(sol.solve(y), x)
+    xo, io = oracle.solve_cr(s.A, s.B, s.y)
+    assert io["status"] == 0 and sol.info_host()[0]["status"] == 0
+    assert np.abs(x.cpu().numpy() - xo).max() <= 1e-11 * np.abs(xo).max()
