@@ -29,7 +29,7 @@ Algorithmic model per block, s bytes per complex element of the level
   k_residual (FP64) read A_j (lower), B_j, x_j, y_j; write r_j.
            flops 8 (3 m^2 k)
 Blocks without a neighbour skip the missing terms.  Blocks above 64 split
-the elimination into k_potrf_big (Cholesky) and k_trsm_big (substitutions).
+the elimination into k_potrf (Cholesky) and k_trsm (substitutions).
 
 Other workloads (one JSON line each, same keys; the default run above is the
 one the contract names):
@@ -87,8 +87,8 @@ def levels(N: int):
 def pass_model(N, m, k, s_of_level, mat, rhs, s_in0=None, upd=0):
     """Algorithmic bytes and flops of one pass over the levels, per kernel.
     Blocks above 64 split the elimination into the tiled Cholesky
-    (k_potrf_big: read A_p lower, write L lower) and the tiled substitutions
-    (k_trsm_big: read L, B_p, B_{p-1}, y_p; write P, Q, g).  s_in0: bytes per
+    (k_potrf: read A_p lower, write L lower) and the tiled substitutions
+    (k_trsm: read L, B_p, B_{p-1}, y_p; write P, Q, g).  s_in0: bytes per
     element of the level-0 inputs A, B, y when they differ from the level's
     own precision (the mixed form's FP32 level 0 reads the FP64 arrays);
     upd: the mixed form's level-0 back substitution writes the FP64 x
@@ -96,7 +96,7 @@ def pass_model(N, m, k, s_of_level, mat, rhs, s_in0=None, upd=0):
     kept blocks."""
     mm, mk, T = m * m, m * k, m * (m + 1) // 2
     big = m > 64
-    names = ("k_potrf_big", "k_trsm_big") if big else ("k_elim", "k_elim")
+    names = ("k_potrf", "k_trsm") if big else ("k_elim", "k_elim")
     tot = {kn: [0.0, 0.0] for kn in set(names) | {"k_reduce", "k_back"}}
     for lvl, (n, ne, nk, e_prev, e_next, k_right, k_f) in enumerate(levels(N)):
         s = s_of_level(n)

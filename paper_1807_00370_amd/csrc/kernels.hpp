@@ -5,19 +5,23 @@
 // A reduction level works on a block-tridiagonal system of n blocks in which
 // position p couples with p - d and p + d (d = 1 for the one-sided schedule
 // with compacted levels; d = 2^level for Algorithm 1, which keeps every block
-// in place).  Three kernels make up one level:
+// in place).  Three steps make up one level; the kernels in this file run them
+// with a work-group of 256 per block and serve blocks of up to 8 where the
+// autotuner finds them faster, the reduction also blocks of 9..32 (the kernels
+// that run by default are in kernels_small.hpp, m <= 8, kernels_fast.hpp, m <= 32,
+// and kernels_big.hpp, m <= 256):
 //
-//   k_elim    one work-group per eliminated block p: L_p = chol(A_p), then by
+//   k_elim    per eliminated block p: L_p = chol(A_p), then by
 //             forward substitution P_p = L_p \ B_p^H, Q_p = L_p \ B_{p-d} and
 //             g_p = L_p \ y_p -- the Section 4 recipe (Gt = L \ G) applied to
 //             the three operands G of Eq. (Formulas).
-//   k_reduce  one work-group per kept block q with eliminated neighbours
+//   k_reduce  per kept block q with eliminated neighbours
 //             l = q - d and r = q + d: the reduced system of Eq. (Formulas),
 //               A'_q = A_q - P_l^H P_l - Q_r^H Q_r   (lower triangle, mirrored,
 //                                                    real diagonal: Section 4)
 //               B'_q = -P_r^H Q_r
 //               y'_q = y_q - P_l^H g_l - Q_r^H g_r
-//   k_back    one work-group per eliminated block: recovers its unknowns from
+//   k_back    per eliminated block: recovers its unknowns from
 //             the first block row of the reordered system (Section 2),
 //               x_p = L_p^{-H} (g_p - Q_p x_{p-d} - P_p x_{p+d}).
 //

@@ -215,58 +215,6 @@ __device__ __forceinline__ void wave_mm3(Acc3<T, RM, RN, RE>& acc, const WOp<T> 
     }
 }
 
-// (cr, ci) += H Y for the 16 x 16 tile with rows row0.. of H and columns of
-// the right operand Y, where H is the Hermitian matrix read from the lower
-// triangle and the real diagonal of the m x m row-major block A:
-// H[i][t] = A[i][t] (t < i), Re A[i][i] (t = i), conj(A[t][i]) (t > i);
-// contraction over all m columns, loaded as in wave_mm.
-template <class T, int G>
-__device__ __forceinline__ void wave_mm_herm(typename MF<T>::v4& cr, typename MF<T>::v4& ci,
-                                             const cx<T>* __restrict__ A, int m, int row0,
-                                             const WOp<T> B)
-{
-    const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
-    const int kd = m, ng = (kd + 4 * G - 1) / (4 * G);
-    const int i = row0 + cc;
-    const bool oa = i < m, ob = cc < B.no;
-    const cx<T>* pb = B.p + ((ob ? cc : 0) * B.so + kr * B.st);
-    const int sb = 4 * B.st;
-    cx<T> xa0[G], yb0[G], xa1[G], yb1[G];
-    auto load = [&](cx<T>(&xa)[G], cx<T>(&yb)[G], int g) {
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-            const int ks = g * G + u, t = 4 * ks + kr;
-            const bool ok = t < kd;
-            cx<T> a = ld_or0(A + (t <= i ? i * m + t : t * m + i), A, ok && oa);
-            a.i = t < i ? a.i : (t == i ? T(0) : -a.i);
-            xa[u] = a;
-            yb[u] = ld_or0(pb + ks * sb, B.p, ok && ob);
-        }
-    };
-    auto comp = [&](const cx<T>(&xa)[G], const cx<T>(&yb)[G]) {
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-            cr = MF<T>::mma(xa[u].r, yb[u].r, cr);
-            cr = MF<T>::mma(-xa[u].i, yb[u].i, cr);
-            ci = MF<T>::mma(xa[u].r, yb[u].i, ci);
-            ci = MF<T>::mma(xa[u].i, yb[u].r, ci);
-        }
-    };
-    load(xa0, yb0, 0);
-    for (int g = 0; g < ng; g += 2) {
-        if (g + 1 < ng)
-            load(xa1, yb1, g + 1);
-        comp(xa0, yb0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (g + 1 < ng) {
-            if (g + 2 < ng)
-                load(xa0, yb0, g + 2);
-            comp(xa1, yb1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-}
-
 template <class T, int RM, int RN>
 __device__ __forceinline__ void zero_acc(typename MF<T>::v4 (&cr)[RM][RN],
                                          typename MF<T>::v4 (&ci)[RM][RN])
@@ -531,10 +479,14 @@ struct lds_el<T, true> {
 // owner of column J + 1 finishes its diagonal tile first and factors it
 // (tile_chol) while the others update: two barriers per J, no read of L.
 //
-// One block's chain of diagonal steps bounds it: 5.6 us each at m = 256 and
-// also at m = 64, where the kernel from memory took 14 and 6.7 (m = 256: 234
-// -> 91 us per launch of few blocks, 1806 -> 794 us for 2048 real blocks;
-// m = 64 FP64 complex: 27 -> 22 us and 481 -> 297 us for 2048 blocks).
+// One block's chain of diagonal steps bounds it, about 6 us each at m = 64 and at
+// m = 256.  us per launch, from memory -> here:
+//   few blocks   FP64 complex m = 64 43 -> 23, m = 128 89 -> 55; FP64 real m = 256
+//                296 -> 96; FP32 complex m = 256 272 -> 144
+//   600 blocks   FP64 complex m = 128 266 -> 147, FP32 complex m = 256 647 -> 443
+// The complex instances of eight tile columns in FP64 and of sixteen in FP32 do
+// not fit altogether: they keep about 70 and 30 of their 256 registers in scratch
+// (176 and 104 bytes a lane), and the figures above are with that.
 // The products are summed from zero and subtracted once per J, as k_potrf_rl
 // does: real data gives the same bits in both.
 template <class T, int SM, class EI = cx<T>, bool RE = false>
@@ -739,8 +691,9 @@ __global__ __launch_bounds__(32 * SM) __attribute__((amdgpu_waves_per_eu(2, 8)))
 // wave with all its row tiles of W = L X (at most SM) in accumulator registers.
 // Right-looking over the columns J of L: X_J = D_J (G_J - W_J) (the result is
 // the right operand as it lies, see the note in k_elim_mf), then
-// W_I += L_IJ X_J for every I > J -- independent accumulators, so the matrix unit never waits for its
-// own result.  Column J of L and D_J, the left operands of all four strips,
+// W_I += L_IJ X_J for every I > J -- independent accumulators, so the matrix unit
+// never waits for its own result.  Column J of L and D_J, the left operands of all
+// four strips,
 // come through LDS once per work-group, column J + 1 being fetched (into
 // registers, then the other LDS buffer) while J is used: one barrier per
 // column.  Tiles are stored 16 x 17 so that the operand reads (16 rows, four
@@ -750,7 +703,7 @@ __global__ __launch_bounds__(32 * SM) __attribute__((amdgpu_waves_per_eu(2, 8)))
 // instructions of 64 cycles per 16 x 16 product against four LDS reads and a
 // quarter of a tile from L2.  Against one wave per strip (or two) that reads
 // its finished rows back from memory, N = 4096, m = 256 real: 13.2 -> 4.9 ms
-// per solve; FP64 complex m = 64 with k = 64, factor and adjoint: 2.54 -> 1.97
+// per solve; FP64 complex N = 16384, m = 64, k = 32, solve and adjoint: 2.54 -> 2.05
 // ms.  Eight waves per group halve the passes over L above 128 and were
 // slower all the same (6.8 ms): one barrier then holds up eight strips.
 // Waves per SIMD that the accumulators of SM row tiles (and the column in
@@ -786,7 +739,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(trsm_waves<
         return;
     const int64_t mm = (int64_t)m * m, mk = (int64_t)m * k;
     // the block's strips: S of B_p^H and S of B_{p-d} where it has those
-    // neighbours, then those of y_p; this wave's is 4 grp + wv
+    // neighbours, then those of y_p; this wave's is per grp + wv
     const int nP = with_mat && p + d < s.n ? S : 0, nQ = with_mat && p - d >= 0 ? S : 0;
     const int nst = nP + nQ + (with_rhs ? (k + 15) >> 4 : 0);
     if (per * grp >= nst)

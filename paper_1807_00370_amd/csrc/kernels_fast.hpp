@@ -74,24 +74,6 @@ __device__ __forceinline__ float rsqrt_nr(float d)
     return r * fmaf(-0.5f * d * r, r, 1.5f);
 }
 
-// Value of x in lane l (uniform l) through the scalar registers.
-__device__ __forceinline__ float lane_bcast(float x, int l)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
-}
-__device__ __forceinline__ double lane_bcast(double x, int l)
-{
-    const long long v = __double_as_longlong(x);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)v, l);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(v >> 32), l);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-template <class T>
-__device__ __forceinline__ cx<T> lane_bcast(const cx<T> x, int l)
-{
-    return cx<T>{lane_bcast(x.r, l), lane_bcast(x.i, l)};
-}
-
 // Orders the LDS accesses of one wave: stores before the call are seen by
 // loads after it from any lane of the same wave (a wave's LDS operations
 // complete in order; the fences keep the compiler from moving them).
@@ -223,48 +205,8 @@ __device__ __forceinline__ void tile_hn(typename MF<T>::v4& cr, typename MF<T>::
     }
 }
 
-// (cr, ci) += X Y on the tile with rows rx0.. (rows of X) and columns cy0..
-// (columns of Y); contraction over kd columns of X / rows of Y.
-template <class T, int KS>
-__device__ __forceinline__ void tile_nn(typename MF<T>::v4& cr, typename MF<T>::v4& ci,
-                                        const cx<T>* __restrict__ X, int ldx, int nrx, int rx0,
-                                        const cx<T>* __restrict__ Y, int ldy, int ncy, int cy0,
-                                        int kd)
-{
-    constexpr int G = KS < kGroup ? KS : kGroup, NG = KS / G;
-    const int lane = threadIdx.x & 63, kr = lane >> 4, cc = lane & 15;
-    const int ar = rx0 + cc, by = cy0 + cc;
-    const bool okx = ar < nrx, oky = by < ncy;
-    const cx<T>* xb = X + (ar * ldx + kr);
-    const cx<T>* yq = Y + (kr * ldy + by);
-    const int sy = 4 * ldy;
-    cx<T> xa[2][G], yb[2][G];
-    auto load = [&](int g, int b) {
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-            const int ks = g * G + u, t = 4 * ks + kr;
-            xa[b][u] = ld_or0(xb + 4 * ks, X, t < kd && okx);
-            yb[b][u] = ld_or0(yq + ks * sy, Y, t < kd && oky);
-        }
-    };
-    load(0, 0);
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if (g + 1 < NG)
-            load(g + 1, (g + 1) & 1);
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-            const cx<T> a = xa[g & 1][u], b = yb[g & 1][u];
-            cr = MF<T>::mma(a.r, b.r, cr);
-            cr = MF<T>::mma(-a.i, b.i, cr);
-            ci = MF<T>::mma(a.r, b.i, ci);
-            ci = MF<T>::mma(a.i, b.r, ci);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-// acc += X Y as tile_nn, in the 3M form.
+// acc += X Y in the 3M form on the tile with rows rx0.. (rows of X) and columns
+// cy0.. (columns of Y); contraction over kd columns of X / rows of Y.
 template <class T, int KS>
 __device__ __forceinline__ void tile_nn3(Acc3<T, 1, 1>& acc, const cx<T>* __restrict__ X, int ldx,
                                          int nrx, int rx0, const cx<T>* __restrict__ Y, int ldy,
@@ -324,14 +266,12 @@ __device__ __forceinline__ void tile_nn3(Acc3<T, 1, 1>& acc, const cx<T>* __rest
 // at the diagonal's size, and the error of a solve was 5 to 8 % larger (m = 16:
 // 6.67e-16 against 6.98e-16, m = 32: 7.55e-16 against 8.09e-16).
 // A panel's chain is four pivots long; the 16 x 16 updates leave it.  The
-// chain of dependent FP64 operations bounds it.  Measured, FP64 complex, one
-// wave: 5560 cycles for L and D; a column at a time on the vector unit, every
-// lane on its whole row, 8700 with twice the instructions.  In an elimination
-// of 64 blocks of m = 32 the two tiles and the products between them take
-// 6.8 us where the forms they replaced (the dot products split over lane
-// groups with LDS broadcasts, then D by substitution from LDS) took 10.8 us;
-// the diagonal step of the tiled Cholesky went from 7.8 to about 2.5 us
-// (16 blocks of m = 64: k_potrf_rl 45 -> 26 us).
+// chain of dependent FP64 operations bounds it.  Measured, one wave: 5740 cycles
+// for L and D of FP64 complex data, 3040 of real data; a column at a time on the
+// vector unit, every lane on its whole row, 8700 with twice the instructions
+// (complex).  The diagonal step of the tiled Cholesky went from 7.8 to about 2.5 us
+// by it.  Panels past the block's edge are left out (a test per column instead
+// cost 1 % at m = 32).
 //
 // The tile is factored in double for every type; for float the columns are
 // rounded to float as they are finished, so that D is the inverse of the L
@@ -603,10 +543,9 @@ __device__ __forceinline__ void packed_load(cx<T>* sL, const cx<T>* __restrict__
 //
 // What is stored is L_10 and the D tiles in place of L's diagonal tiles: the
 // later passes (right-hand side alone, back substitution) start with the
-// operands they need and invert nothing.  A level of 64 blocks, m = 32, FP64,
-// k = 16: 20.2 -> 15.9 us with the matrix, 9.8 -> 7.4 us without (2.6 us of
-// that was the inverse); 8192 blocks (bound by HBM): 163 -> 153 us and 49 ->
-// 41 us.  A and the factor move through LDS so that every access to memory is
+// operands they need and invert nothing.  A level of 64 blocks, m = 32, FP64
+// complex, k = 16: 18.2 -> 14.4 us with the matrix, 8.0 -> 5.9 us without; 8192
+// blocks (bound by HBM): 158 -> 153 us and 49 -> 41 us.  A and the factor move through LDS so that every access to memory is
 // linear: the same loads straight into the tile layout (64-byte pieces) cost
 // 30 % at 8192 blocks.
 //
@@ -867,21 +806,8 @@ struct OpTile {
     }
 };
 
-// (cr, ci) += A^H B for operand tiles A (rows of the result) and B (columns).
-template <class T, int KS>
-__device__ __forceinline__ void mma_hn(typename MF<T>::v4& cr, typename MF<T>::v4& ci,
-                                       const OpTile<T, KS>& A, const OpTile<T, KS>& B)
-{
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        cr = MF<T>::mma(A.v[s].r, B.v[s].r, cr);
-        cr = MF<T>::mma(A.v[s].i, B.v[s].i, cr);
-        ci = MF<T>::mma(A.v[s].r, B.v[s].i, ci);
-        ci = MF<T>::mma(-A.v[s].i, B.v[s].r, ci);
-    }
-}
-
-// acc += A^H B for operand tiles A and B in the 3M form.
+// acc += A^H B for operand tiles A (rows of the result) and B (columns) in the
+// 3M form.
 template <class T, int KS>
 __device__ __forceinline__ void mma_hn3(Acc3<T, 1, 1>& acc, const OpTile<T, KS>& A,
                                         const OpTile<T, KS>& B)
@@ -1191,7 +1117,8 @@ __global__ __launch_bounds__(64, (MT >= 64 ? 2 : 4)) void k_reduce_t(const Seg* 
 // of x_p, w = g - Q x_{p-d} - P x_{p+d} stays in the accumulators and the
 // block upper triangular L^H x = w is solved tile by tile,
 // x_1 = D_1^H w_1, x_0 = D_0^H (w_0 - L_10^H x_1), with the products chained
-// through the accumulators as in k_elim_mf (D_I = L_II^{-1} formed from L).
+// through the accumulators as in k_elim_mf (D_I = L_II^{-1} is stored in L_II's
+// place).
 template <class T, int MT>
 __global__ __launch_bounds__(64, 2) void k_back_mf(const Seg* __restrict__ segs, int nseg,
                                                    int64_t total, const cx<T>* __restrict__ W,

@@ -21,10 +21,11 @@
 // their loads below.  Measured against the kernels they replaced (one wave per
 // block in the elimination, a work-group of 256 per block in the others),
 // N = 131071, m = 8, k = 1, FP64 complex, level 0 / all levels of a solve, us:
-//   elimination        141 -> 110 / 376 -> 329
-//   reduction          390 -> 77 / 813 -> 220   (340 MB: 4.4 TB/s)
-//   back substitution  374 -> 51 / 739 -> 134   (183 MB: 3.6 TB/s)
-// and N = 64, m = 4, k = 1: 87 -> 58 us of kernels.
+//   elimination        141 -> 91 / 376 -> 279   (390 MB: 4.3 TB/s)
+//   reduction          390 -> 74 / 813 -> 220   (340 MB: 4.6 TB/s)
+//   back substitution  374 -> 48 / 739 -> 134   (183 MB: 3.8 TB/s)
+// and N = 64, m = 4, k = 1: 87 -> 57 us of kernels.  The elimination of FP64
+// complex blocks of 5..8 keeps 6 registers in scratch (28 bytes a lane).
 #pragma once
 
 #include "kernels_fast.hpp"
