@@ -699,9 +699,10 @@ __global__ __launch_bounds__(32 * SM) __attribute__((amdgpu_waves_per_eu(2, 8)))
 // column.  Tiles are stored 16 x 17 so that the operand reads (16 rows, four
 // columns) fall on different banks.
 //
-// FP64 MFMA is what bounds it: 16 (four-multiplication form; real data 4)
+// FP64 MFMA is the largest part of its time (busy 36 to 44 % for real data at m =
+// 256, 39 % for complex data at m = 64): 16 (four-multiplication form; real data 4)
 // instructions of 64 cycles per 16 x 16 product against four LDS reads and a
-// quarter of a tile from L2.  Against one wave per strip (or two) that reads
+// quarter of a tile from L2; the rest waits at the barrier of each column.  Against one wave per strip (or two) that reads
 // its finished rows back from memory, N = 4096, m = 256 real: 13.2 -> 4.9 ms
 // per solve; FP64 complex N = 16384, m = 64, k = 32, solve and adjoint: 2.54 -> 2.05
 // ms.  Eight waves per group halve the passes over L above 128 and were
@@ -1261,9 +1262,9 @@ __global__ __launch_bounds__(64) void k_reduce_big(const Seg* __restrict__ segs,
 // NT (NT + 1) / 2 lower tiles of A', then the NT^2 tiles of B' (NT =
 // ceil(m / 64)).  The right-hand-side tiles y' run in k_reduce_big.
 //
-// FP64 MFMA bounds it (complex 67 % busy).  Real data keeps real parts only in
-// LDS, whose bank conflicts held it at 45 %, and leaves out the 16 x 16 tiles
-// without output: N = 4096, m = 256 real 8.85 -> 7.37 ms per solve.  Complex data
+// FP64 MFMA bounds it: at m = 256 it is busy 67 % of the time for complex data and
+// 48 to 55 % for real data, which keeps real parts only in LDS (complex elements
+// there met bank conflicts) and leaves out the 16 x 16 tiles without output: N = 4096, m = 256 real 8.85 -> 7.37 ms per solve.  Complex data
 // runs all four tiles of a quarter: leaving some out cost the loop its
 // schedule (N = 4096, m = 256: 18.3 -> 20.2 ms with y'; with tests inside the
 // loop N = 1023, m = 200 3.87 -> 4.25 ms).
